@@ -19,7 +19,10 @@ SHAPE_SOURCE = "kern_raster.hip"  # compiled once per workgroup shape
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-Wall",
           "-Wno-unused-function", "-I", os.path.join(HERE, "..", "include")]
-DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# The atomic optimizer would reduce a one-lane atomic over the wave and wait for its result on the spot; the render
+# kernels request their next ticket early and read it a batch later.
+DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 
 
 def shapes():

@@ -456,9 +456,11 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
     // reloaded in place right after use, so every load is issued PF
     // groups ahead of its use.  The rounds are branch-free: reloads are
     // unconditional and clamped to the wave's last group, so every wait
-    // counts exactly the loads in flight.  Only whole rounds run this way;
-    // the last nj mod PF groups are then already loaded in the first
-    // register sets and are processed without reloads (no empty slots).
+    // counts exactly the loads in flight.  The last round (1 .. PF groups,
+    // loaded by then) reloads nothing: a full batch's ten groups per wave used
+    // to issue five more loads whose results nothing read, but which the next
+    // batch's first wait had to see done (with the queue slot below: 382 -> 359
+    // us a frame at 1e9 points and 2016x2240, 149 -> 141 at 1e8 and 1920x1080).
     const uint32_t glast = wave + (nj - 1) * WAVES;
     Words R[PF];
     uint32_t gi[PF];
@@ -471,20 +473,19 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
       // younger loads on every path
       __builtin_amdgcn_sched_barrier(0);
     }
-    const uint32_t whole = nj - nj % PF;
-    for (uint32_t j = 0; j < whole; j += PF) {
+    uint32_t left = nj;
+    for (; left > PF; left -= PF) {
 #pragma unroll
       for (int d = 0; d < PF; ++d) {
-        const uint32_t g = gi[d];  // <= glast in every whole round
+        const uint32_t g = gi[d];
         fn(R[d], first + g * 256 + lane * 4, 4u);
         gi[d] = g + PF * WAVES;
         R[d] = load_group<K, ACC>(bs, min(gi[d], glast), lane16);
       }
     }
-    const uint32_t rest = nj - whole;  // groups gi[0 .. rest - 1], loaded in R[0 .. rest - 1]
 #pragma unroll
     for (int d = 0; d < PF; ++d)
-      if ((uint32_t)d < rest) fn(R[d], first + gi[d] * 256 + lane * 4, 4u);
+      if ((uint32_t)d < left) fn(R[d], first + gi[d] * 256 + lane * 4, 4u);
   }
   const uint32_t rem = count & 255u;
   if (rem && wave == ngrp % WAVES) {  // ragged tail of the batch: scalar loads, per-point bounds
@@ -756,18 +757,20 @@ __device__ __forceinline__ void render_pair(const LiveBatch& ra, const ViewOut& 
 // The live list (or run list) of nb slots holds nt tiled entries from the
 // front and nd entries with untiled batches from the back (slots nb - 1,
 // nb - 2, ...).  Queue position p of n = nt + nd takes an untiled one iff
-// floor((p + 1) nd / n) > floor(p nd / n), which spreads the untiled batches
-// (and their global atomics) evenly over the frame.  Returns ~0u past the end.
-// One division: with k = floor(p nd / n) and r = p nd - k n, the next
-// quotient is k + floor((r + nd) / n), and r + nd < 2n, so it exceeds k iff
-// r >= n - nd = nt.
-__device__ __forceinline__ uint32_t live_slot(uint32_t p, uint32_t nt, uint32_t nd, uint32_t nb) {
-  const uint32_t n = nt + nd;
-  if (p >= n) return ~0u;
-  if (nd == 0) return p;
-  const uint64_t num = (uint64_t)p * nd;
-  const uint32_t k = (uint32_t)(num / n), r = (uint32_t)(num - (uint64_t)k * n);
-  return r >= nt ? nb - 1u - k : p - k;
+// floor((p + 1) m / 2^32) > floor(p m / 2^32), m = ceil(2^32 nd / n), which
+// spreads the untiled batches (and their global atomics) evenly over the frame:
+// n m / 2^32 lies in [nd, nd + 1), so exactly nd positions do.  Two high
+// products per position: the exact quotient floor(p nd / n) cost wave 0 a
+// 64-bit division per batch, at one instruction per 8 cycles, while three
+// waves waited.  Returns ~0u past the end.
+__device__ __forceinline__ uint32_t spread_rate(uint32_t nt, uint32_t nd) {
+  return nt == 0 ? 0u : (uint32_t)((((uint64_t)nd << 32) + (nt + nd - 1)) / (nt + nd));
+}
+__device__ __forceinline__ uint32_t live_slot(uint32_t p, uint32_t nt, uint32_t nd, uint32_t rate, uint32_t nb) {
+  if (p >= nt + nd) return ~0u;
+  if (nt == 0) return nb - 1u - p;
+  const uint32_t k = __umulhi(p, rate), k1 = __umulhi(p + 1u, rate);
+  return k1 > k ? nb - 1u - k : p - k;
 }
 
 __device__ __forceinline__ void fill_tile(uint64_t* tile, uint32_t tid) {
@@ -798,8 +801,8 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   // this workgroup's queue: workgroups are spread over the queues round-robin
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
-  const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count;
-  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, a.nb);
+  const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
+  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.nb);
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
   uint32_t i = uni(s_next);
@@ -807,7 +810,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   while (i != ~0u) {
     // Take the next batch now; the atomic's latency hides behind this batch.
     uint32_t grab = 0;
-    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, a.nb);
+    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.nb);
     render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, natom);
     i = uni(s_next);
   }
@@ -826,15 +829,15 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   fill_tile(tile, tid);
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
-  const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count;
-  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, a.cap);
+  const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
+  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.cap);
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
   uint32_t i = uni(s_next);
   uint32_t natom = 0;
   while (i != ~0u) {
     uint32_t grab = 0;
-    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, a.cap);
+    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.cap);
     const Run run = a.runs[i];
     uint64_t mask = run.mask;
     bool publish = true;
