@@ -52,6 +52,8 @@ constexpr uint32_t RENDER_QUEUES = 8;
 // tile wide and max_bands tiles large is rendered in bands of rows that fit
 // the tile (max_bands: a tuning; 1 = no bands).
 constexpr uint32_t DEFAULT_BANDS = 4, MAX_BANDS = 64;
+// Slices that a batch of a frame with few batches is cut into at most (raster_core.h).
+constexpr uint32_t MAX_SLICE_SHIFT = 4, MAX_SLICES = 1u << MAX_SLICE_SHIFT;
 struct FrameHeader {
   // One 64-bit counter (classify adds tiled | untiled << 32 with one atomic
   // per wave, so the two prefixes it returns come from one order):

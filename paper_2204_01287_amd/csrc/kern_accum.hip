@@ -60,21 +60,17 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
   // batch order (Morton order for sorted clouds): the sums' lines of neighbouring
   // batches stay in the caches; measured faster than the render's order here
   const uint32_t nlive = a.hdr->live_count + a.hdr->direct_count;
-  if (tid == 0) {
-    const uint32_t p = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-    s_next = p < nlive ? a.order[p] : ~0u;
-  }
+  const uint32_t shift = slice_shift(nlive, gridDim.x);
+  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, a.colors};
   __syncthreads();
-  uint32_t i = uni(s_next);
+  uint32_t p = uni(s_next);
   uint32_t natom = 0;
-  while (i != ~0u) {
+  while (p >> shift < nlive) {
+    const uint32_t slice = p & ((1u << shift) - 1u);
     uint32_t grab = 0;
-    if (tid == 0) {
-      const uint32_t p = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-      grab = p < nlive ? a.order[p] : ~0u;
-    }
-    const LiveBatch& rec = a.live[i];
+    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+    const LiveBatch& rec = a.live[uni(a.order[p >> shift])];
     Loop L;
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -89,7 +85,7 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     L.acc = a.accum;
     L.thr = thr;
     const uint32_t mode = rec.mode, rxy = rec.rect_xy, rwh = rec.rect_wh;
-    const uint32_t first = rec.first, count = rec.count;
+    Span b = {rec.first, rec.count};
     const uint32_t x0 = rxy & 0xFFFFu, y0 = rxy >> 16;
     L.tw = rwh & 0xFFFFu;
     L.th = rwh >> 16;
@@ -101,22 +97,36 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     // one tile wide: band by band (stage the band's thresholds, add, flush)
     const bool banded = !tiled && k == 10 && ((mode >> 16) & 3u) && L.tw <= HQS_TILE;
     if (banded) {
-      const uint32_t th = L.th, bh = HQS_TILE / L.tw;
+      const uint32_t bh = HQS_TILE / L.tw;
+      uint32_t by0 = 0, by1 = L.th;
+      if (shift) {
+        b = banded_part({uni(b.first), uni(b.count)}, uni(L.th), bh, slice, shift, by0, by1);
+        if (b.count == 0) {  // nothing in this slice
+          by0 = 0;
+          by1 = 1;
+        }
+      }
+      const uint32_t first = b.first, count = b.count;
       L.cx = in_vgpr(uni(0x4B000000u + x0));
-      for (uint32_t by = 0; by < th; by += bh) {
-        L.th = min(bh, th - by);
+      for (uint32_t by = by0; by < by1; by += bh) {
+        L.th = min(bh, by1 - by);
         L.cy = in_vgpr(uni(0x4B000000u + y0 + by));
         stage_band(a, thr, sums, tid, x0, y0 + by, L.tw, L.th);
         __syncthreads();
         raster_by_class<10, true, true, true>(cls, L, st, sums, first, count, wave, lane, natom);
         __syncthreads();  // the band's sums are complete; s_next has been read
-        if (by == 0 && tid == 0) s_next = grab;
+        if (by == by0 && tid == 0) s_next = grab;
         flush_band(a, sums, tid, x0, y0 + by, L.tw, L.th);
         __syncthreads();  // tile free again
       }
-      i = uni(s_next);
+      p = uni(s_next);
       continue;
     }
+    if (shift) {
+      b = {uni(b.first), uni(b.count)};
+      b = tiled ? tiled_part(b, uni(n), slice, shift) : points_part(b, slice, 1u << shift);
+    }
+    const uint32_t first = b.first, count = b.count;
     L.cx = in_vgpr(uni(0x4B000000u + (tiled ? x0 : 0u)));
     L.cy = in_vgpr(uni(0x4B000000u + (tiled ? y0 : 0u)));
     if (tiled) {
@@ -134,7 +144,7 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     if (tid == 0) s_next = grab;
     if (tiled) flush_band(a, sums, tid, x0, y0, L.tw, L.th);
     __syncthreads();  // tile free for the next batch; s_next visible
-    i = uni(s_next);
+    p = uni(s_next);
   }
 }
 
@@ -182,7 +192,8 @@ hipError_t launch_accumulate(const RenderArgs& a, hipStream_t s) {
   if (a.nb == 0) return hipGetLastError();
   // the shading pass walks the render's live list with fresh work-queue counters
   hipLaunchKernelGGL(k_reset_queues, dim3(1), dim3(64), 0, s, a.hdr);
-  const uint32_t blocks_r = a.grid < a.nb ? a.grid : a.nb;
+  const uint64_t items = (uint64_t)a.nb << MAX_SLICE_SHIFT;
+  const uint32_t blocks_r = a.grid < items ? a.grid : (uint32_t)items;
   hipLaunchKernelGGL(k_accum, dim3(blocks_r), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }

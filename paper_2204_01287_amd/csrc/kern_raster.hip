@@ -11,7 +11,9 @@ constexpr int SW = WAVES, SD = PREFETCH, ST = (int)TILE_MAX;
 
 hipError_t render(const RenderArgs& a, hipStream_t s) {
   if (a.nb == 0) return hipSuccess;
-  const uint32_t blocks = a.grid < a.nb ? a.grid : a.nb;
+  // up to 1 << MAX_SLICE_SHIFT queue items per batch
+  const uint64_t items = (uint64_t)a.nb << MAX_SLICE_SHIFT;
+  const uint32_t blocks = a.grid < items ? a.grid : (uint32_t)items;
   if (a.counters)
     hipLaunchKernelGGL((k_render<true, SW, SD, ST>), dim3(blocks), dim3(THREADS), 0, s, a);
   else
@@ -21,7 +23,8 @@ hipError_t render(const RenderArgs& a, hipStream_t s) {
 
 hipError_t render_views(const RenderViewsArgs& a, uint64_t max_runs, int counters, hipStream_t s) {
   if (max_runs == 0) return hipSuccess;
-  const uint32_t blocks = a.grid < max_runs ? a.grid : (uint32_t)max_runs;
+  const uint64_t items = max_runs << MAX_SLICE_SHIFT;
+  const uint32_t blocks = a.grid < items ? a.grid : (uint32_t)items;
   if (counters)
     hipLaunchKernelGGL((k_render_views<true, SW, SD, ST>), dim3(blocks), dim3(THREADS), 0, s, a);
   else

@@ -110,11 +110,24 @@ uint32_t shape_tile(const pr_tuning& t) {
   const uint32_t full = shape_of(t).tile;
   return t.tile_px && t.tile_px < full ? t.tile_px : full;
 }
-uint32_t tune_bands(const pr_tuning& t) { return t.max_bands ? t.max_bands : ptr::DEFAULT_BANDS; }
 uint32_t shape_grid(const pr_ctx* ctx, const pr_tuning& t, int views) {
   uint32_t per = ctx->per_cu[t.shape][views];
   if (t.wg_per_cu && t.wg_per_cu < per) per = t.wg_per_cu;
   return per * ctx->cus;
+}
+
+// The band limit of a frame of items batches (or runs).  Every band streams the
+// batch's points again, which is worth it up to DEFAULT_BANDS tiles; but where
+// the batches leave workgroups idle, a batch's bands run side by side as its
+// slices (raster_core.h), up to as many as a batch has.  With fewer than four
+// batches per band too few points meet on a pixel for the tile to save atomics
+// (1e6 points in 98 batches, bands up to 16: 40 us against 65; 2e4 in 2: 12 against 9).
+uint32_t tune_bands(const pr_tuning& t, uint64_t items, uint32_t grid) {
+  if (t.max_bands) return t.max_bands;
+  uint64_t bands = items ? 2ull * grid / items : 0;
+  if (bands > items / 4) bands = items / 4;
+  if (bands > ptr::MAX_SLICES) bands = ptr::MAX_SLICES;
+  return bands > ptr::DEFAULT_BANDS ? (uint32_t)bands : ptr::DEFAULT_BANDS;
 }
 
 // Pixel-space matrix (Sec. 3.2 projection; the paper leaves toPixelID open):
@@ -466,7 +479,7 @@ pr_status render_frame(pr_ctx* ctx, const pr_cloud* cloud, const float view[16],
   const pr_tuning tune = ctx->tuning;
   a.grid = shape_grid(ctx, tune, 0);
   a.tile_max = shape_tile(tune);
-  a.max_bands = tune_bands(tune);
+  a.max_bands = tune_bands(tune, cloud->nb, a.grid);
   a.vb = visbuf;
   a.stats = ctx->dev->stats;
   frame_matrix(view, proj, w, h, a.Pm);
@@ -602,7 +615,7 @@ pr_status render_views(pr_ctx* ctx, const pr_cloud* cloud, const pr_view* views,
     k.nodes = cloud->lod ? static_cast<const ptr::LodNode*>(cloud->bufs.nodes) : nullptr;
     k.lod_px = o.lod_px;
     k.tile_max = shape_tile(tune);
-    k.max_bands = tune_bands(tune);
+    k.max_bands = tune_bands(tune, nb * nchunks, shape_grid(ctx, tune, 1));
     k.cap = (uint32_t)(nb * nchunks);
     for (uint32_t v = 0; v < k.nchunk; ++v) {
       const pr_view& pv = views[k.view0 + v];

@@ -591,6 +591,56 @@ __device__ __forceinline__ void flush_tile(uint64_t* tile, uint32_t tid, uint64_
   }
 }
 
+// Slices.  A frame of fewer live batches than workgroups would leave most of
+// the chip idle behind one long chain of loads per batch, so each batch is cut
+// into 1 << shift queue items, enough for two per workgroup and 16 at most
+// (finer ones lose more to further flushes than the idle workgroups give: 1e6
+// points in 98 batches 46 us at 32 slices against 40 at 16).  Slice s of a
+// batch takes a share of its points, in whole groups of 256 (the smallest work
+// of a wave).  A tiled batch stays in as few parts as keep the flushes (one of
+// the whole rectangle per part) below the work on the points; a banded one
+// deals out its bands first, so that a part streams its points for one band
+// only.  Slices without a part do nothing.  Frames of as many batches as
+// workgroups or more are not cut: slices of their last batches alone gained
+// nothing.  Pass times, before and after: 2e4 points at 641x479 51 -> 18 us,
+// 2e5 at 2116x1607 37 -> 21, 1e6 at 1280x720 60 -> 50, shading of 1.2e5 points
+// at 1206x751 150 -> 39.
+__device__ __forceinline__ uint32_t slice_shift(uint32_t items, uint32_t grid) {
+  uint32_t shift = 0;
+  while (shift < MAX_SLICE_SHIFT && (items << shift) < 2u * grid) ++shift;
+  return items < grid ? shift : 0u;
+}
+struct Span {
+  uint32_t first, count;
+};
+__device__ __forceinline__ Span points_part(Span b, uint32_t part, uint32_t parts) {
+  const uint32_t groups = b.count / 256u + (b.count % 256u != 0u);
+  const uint32_t per = (groups + parts - 1u) / parts * 256u, off = part * per;
+  if (part >= parts || off >= b.count) return {b.first, 0u};
+  return {b.first + off, min(per, b.count - off)};
+}
+// The part of a tiled batch of area pixels.
+__device__ __forceinline__ Span tiled_part(Span b, uint32_t area, uint32_t slice, uint32_t shift) {
+  uint32_t parts = 1u << shift;
+  while (parts > 1u && (uint64_t)parts * area > 4ull * b.count) parts >>= 1;
+  return points_part(b, slice, parts);
+}
+// The part of a banded batch of rows th in bands of bh: its points and its rows [y0, y1).
+__device__ __forceinline__ Span banded_part(Span b, uint32_t th, uint32_t bh, uint32_t slice, uint32_t shift,
+                                            uint32_t& y0, uint32_t& y1) {
+  const uint32_t k = 1u << shift, bands = (th + bh - 1u) / bh;
+  if (bands >= k) {
+    const uint32_t per = (bands + k - 1u) / k * bh;
+    y0 = min(slice * per, th);
+    y1 = min(y0 + per, th);
+    return y0 < y1 ? b : Span{b.first, 0u};
+  }
+  const uint32_t parts = k / bands, band = slice / parts;
+  y0 = min(band * bh, th);
+  y1 = min(y0 + bh, th);
+  return y0 < y1 ? points_part(b, slice % parts, parts) : Span{b.first, 0u};
+}
+
 // One live batch of one view by the whole workgroup: its points into the LDS
 // tile (or straight into the global buffer), then the tile flush.  The LDS
 // tile is all PR_EMPTY between batches (the flush resets what it reads), so a
@@ -598,11 +648,12 @@ __device__ __forceinline__ void flush_tile(uint64_t* tile, uint32_t tid, uint64_
 // banded batch (rectangle up to a few tiles, at most one tile wide) streams its
 // points once per band of rows that fits the tile, with the same two barriers
 // per band.  publish: thread 0 stores next into s_next after the first
-// barrier (the workgroup reads it after the last one).
+// barrier (the workgroup reads it after the last one).  slice, shift: the part
+// of the batch to render (above; shift 0: all of it).
 __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, uint32_t H, uint64_t* vb,
                                              const Streams& st, uint64_t* tile, uint32_t tid, uint32_t wave,
                                              uint32_t lane, bool publish, uint32_t next, uint32_t* s_next,
-                                             uint32_t& natom) {
+                                             uint32_t slice, uint32_t shift, uint32_t& natom) {
   Loop L;
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
@@ -614,7 +665,7 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   L.H = H;
   L.vb = vb;
   const uint32_t mode = rec.mode, rxy = rec.rect_xy, rwh = rec.rect_wh;
-  const uint32_t first = rec.first, count = rec.count;
+  Span b = {rec.first, rec.count};
   const uint32_t x0 = rxy & 0xFFFFu, y0 = rxy >> 16;
   L.tw = rwh & 0xFFFFu;
   L.th = rwh >> 16;
@@ -622,20 +673,34 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   const int k = (int)(mode & 0xFFu), cls = (int)((mode >> 8) & 0xFFu);
   const bool tiled = (mode >> 16) & 1u;
   if ((mode >> 17) & 1u) {
-    const uint32_t th = L.th, bh = TILE_MAX / L.tw;  // rows per band (the rectangle is at most one tile wide)
+    const uint32_t bh = TILE_MAX / L.tw;  // rows per band (the rectangle is at most one tile wide)
+    uint32_t by0 = 0, by1 = L.th;
+    if (shift) {
+      b = banded_part({uni(b.first), uni(b.count)}, uni(L.th), bh, slice, shift, by0, by1);
+      if (b.count == 0) {  // nothing in this slice
+        by0 = 0;
+        by1 = 1;
+      }
+    }
+    const uint32_t first = b.first, count = b.count;
     L.cx = in_vgpr(uni(0x4B000000u + x0));
-    for (uint32_t by = 0; by < th; by += bh) {
-      L.th = min(bh, th - by);
+    for (uint32_t by = by0; by < by1; by += bh) {
+      L.th = min(bh, by1 - by);
       L.cy = in_vgpr(uni(0x4B000000u + y0 + by));
       // classify bands 10-bit batches only (more levels here would raise the kernel's register count)
       raster_by_class<10, true, false, true>(cls, L, st, tile, first, count, wave, lane, natom);
       __syncthreads();  // the band's points are all in the tile; s_next has been read
-      if (by == 0 && publish && tid == 0) *s_next = next;
+      if (by == by0 && publish && tid == 0) *s_next = next;
       flush_tile(tile, tid, L.vb, L.W, x0, y0 + by, L.tw, L.th, natom);
       __syncthreads();  // tile clean again
     }
     return;
   }
+  if (shift) {
+    b = {uni(b.first), uni(b.count)};
+    b = tiled ? tiled_part(b, uni(L.tw * L.th), slice, shift) : points_part(b, slice, 1u << shift);
+  }
+  const uint32_t first = b.first, count = b.count;
   L.cx = in_vgpr(uni(0x4B000000u + (tiled ? x0 : 0u)));
   L.cy = in_vgpr(uni(0x4B000000u + (tiled ? y0 : 0u)));
   if (tiled) {
@@ -649,7 +714,7 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   }
   __syncthreads();  // the batch's points are all in the tile; s_next has been read
   if (publish && tid == 0) *s_next = next;
-  if (tiled) flush_tile(tile, tid, L.vb, L.W, x0, y0, L.tw, L.th, natom);
+  if (tiled && count != 0) flush_tile(tile, tid, L.vb, L.W, x0, y0, L.tw, L.th, natom);
   __syncthreads();  // tile clean again; s_next visible
 }
 
@@ -695,13 +760,15 @@ constexpr int PAIR_PF = PREFETCH < 3 ? PREFETCH : 3;
 __device__ __forceinline__ void render_pair(const LiveBatch& ra, const ViewOut& va, const LiveBatch& rb,
                                             const ViewOut& vb, const Streams& st, uint64_t* tile, uint32_t tid,
                                             uint32_t wave, uint32_t lane, bool publish, uint32_t next,
-                                            uint32_t* s_next, uint32_t& natom) {
+                                            uint32_t* s_next, uint32_t slice, uint32_t shift, uint32_t& natom) {
   const Loop A = tiled_loop(ra, va.W, va.H, va.vb);
   Loop B = tiled_loop(rb, vb.W, vb.H, vb.vb);
   const uint32_t na = uni(rect_area(ra));
   B.base8 = na * 8u;
   // uniform by construction (one record per workgroup); said so for the compiler
-  const uint32_t first = uni(ra.first), count = uni(ra.count);
+  Span part = {uni(ra.first), uni(ra.count)};
+  if (shift) part = tiled_part(part, na + uni(rect_area(rb)), slice, shift);
+  const uint32_t first = part.first, count = part.count;
   const int ca = (int)((uni(ra.mode) >> 8) & 0xFFu), cb = (int)((uni(rb.mode) >> 8) & 0xFFu);
   // y and w rows bit-equal in both records: shared chains
   bool shared = true;
@@ -749,8 +816,10 @@ __device__ __forceinline__ void render_pair(const LiveBatch& ra, const ViewOut& 
   }
   __syncthreads();  // both views' points are in their sub-tiles; s_next has been read
   if (publish && tid == 0) *s_next = next;
-  flush_tile(tile, tid, va.vb, va.W, ra.rect_xy & 0xFFFFu, ra.rect_xy >> 16, A.tw, A.th, natom);
-  flush_tile(tile + na, tid, vb.vb, vb.W, rb.rect_xy & 0xFFFFu, rb.rect_xy >> 16, B.tw, B.th, natom);
+  if (count != 0) {
+    flush_tile(tile, tid, va.vb, va.W, ra.rect_xy & 0xFFFFu, ra.rect_xy >> 16, A.tw, A.th, natom);
+    flush_tile(tile + na, tid, vb.vb, vb.W, rb.rect_xy & 0xFFFFu, rb.rect_xy >> 16, B.tw, B.th, natom);
+  }
   __syncthreads();  // tile clean again; s_next visible
 }
 
@@ -802,17 +871,19 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.nb);
+  const uint32_t shift = slice_shift(nt + nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
-  uint32_t i = uni(s_next);
+  uint32_t p = uni(s_next), i = live_slot(p >> shift, nt, nd, rate, a.nb);
   uint32_t natom = 0;
   while (i != ~0u) {
-    // Take the next batch now; the atomic's latency hides behind this batch.
+    // Take the next position now; the atomic's latency hides behind this batch.
     uint32_t grab = 0;
-    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.nb);
-    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, natom);
-    i = uni(s_next);
+    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift, natom);
+    p = uni(s_next);
+    i = live_slot(p >> shift, nt, nd, rate, a.nb);
   }
   add_atomics<CNT>(a.stats, natom, lane);
 }
@@ -830,14 +901,15 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  if (tid == 0) s_next = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.cap);
+  const uint32_t shift = slice_shift(nt + nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
-  uint32_t i = uni(s_next);
+  uint32_t p = uni(s_next), i = live_slot(p >> shift, nt, nd, rate, a.cap);
   uint32_t natom = 0;
   while (i != ~0u) {
     uint32_t grab = 0;
-    if (tid == 0) grab = live_slot(atomicAdd(qc, 1u) * RENDER_QUEUES + q, nt, nd, rate, a.cap);
+    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
     const Run run = a.runs[i];
     uint64_t mask = run.mask;
     bool publish = true;
@@ -853,16 +925,18 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
         const LiveBatch& rec2 = recs[v2];
         if (pairable(rec2) && rect_area(rec) + rect_area(rec2) <= TILE_MAX) {
           mask &= mask - 1;
-          render_pair(rec, a.v[v], rec2, a.v[v2], st, tile, tid, wave, lane, publish, grab, &s_next, natom);
+          render_pair(rec, a.v[v], rec2, a.v[v2], st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift,
+                      natom);
           publish = false;
           continue;
         }
       }
       const ViewOut& vo = a.v[v];
-      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, natom);
+      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift, natom);
       publish = false;
     }
-    i = uni(s_next);
+    p = uni(s_next);
+    i = live_slot(p >> shift, nt, nd, rate, a.cap);
   }
   add_atomics<CNT>(a.stats, natom, lane);
 }
