@@ -203,31 +203,46 @@ hipError_t launch_stream(const void* src, void* dst, uint64_t bytes, uint64_t* s
 struct SortScratch {
   uint64_t* keys0;
   uint64_t* keys1;
-  uint32_t* vals1;  // vals0 is the caller's perm buffer
-  uint32_t* hist;   // 256 * nblk
+  uint32_t* vals1;  // the other value buffer is the caller's perm buffer
+  uint32_t* hist;   // digits * nblk
   uint32_t* part;   // scan partial sums
   uint32_t* aabb;   // 6 ordered keys: min x,y,z then max x,y,z
   uint64_t nblk, npart;
+  uint64_t end;     // bytes of the scratch buffer used
 };
-// Scratch layout for n points (a Morton order); returns total bytes.
-uint64_t sort_scratch_layout(uint64_t n, uint8_t* base, SortScratch* out);
+// Scratch bytes that a Morton order of n points asks of the caller, after the small scratch.
+uint64_t sort_scratch_bytes(uint64_t n);
 uint64_t small_scratch_bytes();
+// The areas of a scratch buffer of small_scratch_bytes() + sort_scratch_bytes(n).
+void sort_scratch_layout(uint64_t n, uint8_t* scratch, SortScratch* out);
 
 hipError_t launch_finite_check(const float* xyz, uint64_t n, uint32_t* flag, hipStream_t s);
 hipError_t launch_iota(uint32_t* p, uint64_t n, hipStream_t s);
-// cloud box (with the finite check: flag) and Morton codes
-hipError_t launch_morton_codes(const float* xyz, uint64_t n, uint32_t* aabb, uint64_t* keys, uint32_t* vals,
-                               uint32_t* flag, hipStream_t s);
-hipError_t radix_sort_pairs(const SortScratch& sc, uint32_t* vals0, uint64_t n, hipStream_t s);
-// positions and colours in sorted order (perm[sorted] = original), through
-// 16-byte records in the key buffers (xyz_out may be xyz: the gather reads
-// the records)
-// spread: every batch of batch_size points (the last one shorter) in the spread
-// order (position r <- Morton rank (r * m) mod c, m = spread_step(c)); perm is
-// then rewritten in that order
-hipError_t launch_gather(const SortScratch& sc, const float* xyz, const uint32_t* rgba, uint32_t* perm,
-                         uint64_t n, uint32_t batch_size, bool spread, float* xyz_out, uint32_t* colors,
-                         hipStream_t s);
+// The stable Morton order of the points: sc.vals1[rank] = index (perm: working
+// memory).  nonfinite: set if a coordinate is NaN or Inf.  full: every bit of
+// the codes by radix passes; else the leading bits, and the runs they leave
+// equal in LDS, with unsorted set if a run was too long for that (the order is
+// then wrong and the caller sorts again in full).
+hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, bool full,
+                              uint32_t* nonfinite, uint32_t* unsorted, hipStream_t s);
+struct BuildArgs {
+  float* xyz;
+  const uint32_t* rgba;
+  uint64_t n;
+  uint32_t S;
+  uint32_t *colors, *perm;
+  BatchRec* batches;
+  uint32_t *low, *med, *high;
+  uint32_t* nonfinite;
+};
+// Batches of a.S points in input order, with the finite check: colours, perm, boxes, words.
+hipError_t launch_build_input(const BuildArgs& a, hipStream_t s);
+// The same in the order of sc.vals1 (positions too, in place), through 16-byte
+// records in the key buffers.  spread: every batch (the last one shorter) in the
+// spread order (position r <- Morton rank (r * m) mod c, m = spread_step(c)).
+hipError_t launch_build_sorted(const BuildArgs& a, const SortScratch& sc, bool spread, hipStream_t s);
+// The input positions again, from the records of launch_build_sorted.
+hipError_t launch_restore(const SortScratch& sc, uint64_t n, float* xyz, hipStream_t s);
 // the first integer >= floor(c / 4) + 1 coprime with c
 uint64_t spread_step(uint64_t c);
 hipError_t launch_batch_bbox(const float* xyz, uint64_t n, uint32_t S, uint64_t nb, BatchRec* out, hipStream_t s);

@@ -1,9 +1,9 @@
 // Load-time build kernels for gfx950 (Sec. 3.1 data structure, Sec. 3.3 Eq. 1).
 //
-//  finite check (with the Morton order: on the cloud box's loads) -> [cloud
-//  box -> 63-bit Morton codes -> stable LSD radix sort
-//  (8 passes of 8 bits) -> gather] -> per-batch boxes -> Eq. 1 quantise and
-//  split into low / med / high words.
+//  Morton orders: cloud box and finite check -> 63-bit Morton codes -> stable
+//  sort (radix passes over the code's leading bits, then the runs that these
+//  leave equal, in LDS) -> records of position and colour -> per batch: gather,
+//  box, Eq. 1 words (one kernel).  Input order: the last kernel alone.
 //
 // Boxes order binary32 values by IEEE totalOrder (-0 below +0) through the
 // monotone integer map okey(), so a box depends only on the point set, not on
@@ -21,6 +21,15 @@ __device__ __forceinline__ float okey_inv(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
+// Workgroups are dealt to the eight XCDs in turn, each with an L2 of its own.
+// Where neighbouring tiles write parts of the same lines, or read them, workgroup
+// b takes tile (b mod 8) per + b / 8 instead of tile b: an XCD then works on one
+// contiguous eighth and its L2 puts the parts together.  The grid is 8 per; a
+// tile at or past tiles is none.
+constexpr uint32_t XCDS = 8;
+inline uint32_t xcd_grid(uint64_t tiles) { return (uint32_t)((tiles + XCDS - 1) / XCDS * XCDS); }
+__device__ __forceinline__ uint32_t xcd_tile() { return blockIdx.x % XCDS * (gridDim.x / XCDS) + blockIdx.x / XCDS; }
+
 // ---------------------------------------------------------- finite check
 __global__ void __launch_bounds__(256) k_finite(const uint32_t* __restrict__ w, uint64_t nwords,
                                                 uint32_t* __restrict__ flag) {
@@ -37,40 +46,92 @@ __global__ void __launch_bounds__(256) k_iota(uint32_t* __restrict__ p, uint64_t
 }
 
 // ------------------------------------------------------------- cloud box
-__global__ void k_aabb_init(uint32_t* aabb) {
-  if (threadIdx.x < 6) aabb[threadIdx.x] = threadIdx.x < 3 ? 0xFFFFFFFFu : 0u;
+struct Box {
+  uint32_t mn[3], mx[3];
+};
+__device__ __forceinline__ Box empty_box() {
+  return {{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, {0u, 0u, 0u}};
 }
-
-// The cloud box, and the finite check on the same loads (flag: set if a
-// coordinate is NaN or Inf).
-__global__ void __launch_bounds__(256) k_aabb(const float* __restrict__ xyz, uint64_t n, uint32_t* __restrict__ aabb,
-                                              uint32_t* __restrict__ flag) {
-  uint32_t mn[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, mx[3] = {0, 0, 0};
-  bool bad = false;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const float f = xyz[3 * i + a];
-      bad |= (__float_as_uint(f) & 0x7F800000u) == 0x7F800000u;
-      const uint32_t k = okey(f);
-      mn[a] = min(mn[a], k);
-      mx[a] = max(mx[a], k);
-    }
-  }
-  if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+__device__ __forceinline__ void grow(Box& b, int a, float f) {
+  const uint32_t k = okey(f);
+  b.mn[a] = min(b.mn[a], k);
+  b.mx[a] = max(b.mx[a], k);
+}
+// The workgroup's box (every thread gets it).  red: LDS, one Box per wave.
+__device__ __forceinline__ Box block_box(Box b, Box* red) {
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     for (int o = 32; o > 0; o >>= 1) {
-      mn[a] = min(mn[a], (uint32_t)__shfl_xor((int)mn[a], o));
-      mx[a] = max(mx[a], (uint32_t)__shfl_xor((int)mx[a], o));
+      b.mn[a] = min(b.mn[a], (uint32_t)__shfl_xor((int)b.mn[a], o));
+      b.mx[a] = max(b.mx[a], (uint32_t)__shfl_xor((int)b.mx[a], o));
     }
   }
-  if ((threadIdx.x & 63) == 0) {
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
+  __syncthreads();
+  for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      atomicMin(&aabb[a], mn[a]);
-      atomicMax(&aabb[3 + a], mx[a]);
+      b.mn[a] = min(b.mn[a], red[w].mn[a]);
+      b.mx[a] = max(b.mx[a], red[w].mx[a]);
+    }
+  }
+  return b;
+}
+__device__ __forceinline__ bool not_finite(float f) { return (__float_as_uint(f) & 0x7F800000u) == 0x7F800000u; }
+__device__ __forceinline__ void raise(uint32_t* flag, bool bad) {
+  if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+}
+
+// The cloud box, and the finite check on the same loads (flag: set if a
+// coordinate is NaN or Inf).  One box per workgroup, reduced by a second
+// launch: 4,096 workgroups combining theirs by atomics on one line took 1.14
+// ms for any cloud (28 % of a 2e7-point build), 40 us with the partial boxes.
+constexpr uint32_t BOX_BLOCKS = 1024;
+__global__ void __launch_bounds__(256) k_aabb(const float* __restrict__ xyz, uint64_t n, Box* __restrict__ part,
+                                              uint32_t* __restrict__ flag) {
+  __shared__ Box red[4];
+  Box box = empty_box();
+  bool bad = false;
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x, n4 = n / 4;
+  const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const float4* const v4 = reinterpret_cast<const float4*>(xyz);
+  for (uint64_t g = t0; g < n4; g += stride) {  // four points: three 16-byte loads
+    const float4 u = v4[3 * g], v = v4[3 * g + 1], w = v4[3 * g + 2];
+    const float f[12] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w, w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int j = 0; j < 12; ++j) {
+      bad |= not_finite(f[j]);
+      grow(box, j % 3, f[j]);
+    }
+  }
+  for (uint64_t i = 4 * n4 + t0; i < n; i += stride) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      bad |= not_finite(xyz[3 * i + a]);
+      grow(box, a, xyz[3 * i + a]);
+    }
+  }
+  raise(flag, bad);
+  box = block_box(box, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = box;
+}
+__global__ void __launch_bounds__(256) k_aabb_top(const Box* __restrict__ part, uint32_t blocks,
+                                                  uint32_t* __restrict__ aabb) {
+  __shared__ Box red[4];
+  Box box = empty_box();
+  for (uint32_t i = threadIdx.x; i < blocks; i += 256) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      box.mn[a] = min(box.mn[a], part[i].mn[a]);
+      box.mx[a] = max(box.mx[a], part[i].mx[a]);
+    }
+  }
+  box = block_box(box, red);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      aabb[a] = box.mn[a];
+      aabb[3 + a] = box.mx[a];
     }
   }
 }
@@ -86,55 +147,99 @@ __device__ __forceinline__ uint64_t spread3(uint64_t x) {  // bit b -> bit 3b (2
   return x;
 }
 
-// q = min(floor(2^21 (x - cmin) / (cmax - cmin)), 2^21 - 1) in binary64; 0 for an empty extent.
-__device__ __forceinline__ uint32_t morton_q(float x, float cmin, float cmax) {
-  const double d = (double)x - (double)cmin;
-  const double s = (double)cmax - (double)cmin;
-  if (s == 0.0) return 0u;
-  const double f = floor((d * 2097152.0) / s);
-  return f > 2097151.0 ? 2097151u : (uint32_t)f;
+// min(floor(fl(d scale / s)), scale - 1) for d = x - lo, s = hi - lo in
+// binary64, scale a power of two up to 2^30, with the quotient rounded once as
+// the contract says; 0 for an empty extent.  The quotient comes from the axis's
+// reciprocal (two roundings, off by less than 2^-20 below 2^30); unless it lies
+// that close to a whole number, its floor is the rounded quotient's floor too.
+// The rest, about one coordinate in 2^19, takes the division.
+struct Axis {
+  double lo, s, inv;  // inv = scale / s, 0 for an empty extent
+};
+__device__ __forceinline__ Axis make_axis(float lo, float hi, double scale) {
+  Axis a;
+  a.lo = (double)lo;
+  a.s = (double)hi - (double)lo;
+  a.inv = a.s == 0.0 ? 0.0 : scale / a.s;
+  return a;
 }
-
-__global__ void __launch_bounds__(256) k_morton(const float* __restrict__ xyz, uint64_t n,
-                                                const uint32_t* __restrict__ aabb, uint64_t* __restrict__ keys,
-                                                uint32_t* __restrict__ vals) {
-  const float cmin[3] = {okey_inv(aabb[0]), okey_inv(aabb[1]), okey_inv(aabb[2])};
-  const float cmax[3] = {okey_inv(aabb[3]), okey_inv(aabb[4]), okey_inv(aabb[5])};
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint64_t qx = morton_q(xyz[3 * i], cmin[0], cmax[0]);
-    const uint64_t qy = morton_q(xyz[3 * i + 1], cmin[1], cmax[1]);
-    const uint64_t qz = morton_q(xyz[3 * i + 2], cmin[2], cmax[2]);
-    keys[i] = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
-    vals[i] = (uint32_t)i;
+__device__ __forceinline__ uint32_t axis_cell(const Axis& a, float x, double scale) {
+  const double d = (double)x - a.lo, q = d * a.inv, f = floor(q), r = q - f;
+  uint32_t c = (uint32_t)f;
+  if (!(r > 0x1p-20 && r < 1.0 - 0x1p-20)) {
+    const double e = a.s == 0.0 ? 0.0 : floor((d * scale) / a.s);
+    c = e > scale - 1.0 ? (uint32_t)(scale - 1.0) : (uint32_t)e;
   }
+  return c;
 }
 
 // ------------------------------------------------------------ radix sort
-// Stable LSD radix sort of (u64 key, u32 value) pairs, 8 bits per pass.
-// Each block owns a tile of RS_TILE consecutive elements.  count: per-block
-// digit histogram, stored digit-major (hist[d * nblk + blk]); an exclusive
-// scan of that array gives every (digit, block) its output offset; scatter:
-// the tile is ranked chunk by chunk in input order (wave ballots give the
-// rank among equal digits inside a wave, LDS counters carry it across waves
-// and chunks), which keeps equal keys in input order.
-constexpr int RS_THREADS = 256;
-constexpr int RS_CHUNKS = 16;
-constexpr uint64_t RS_TILE = (uint64_t)RS_THREADS * RS_CHUNKS;
+// Stable LSD radix sort of (u64 key, u32 value) pairs, RS_BITS bits per pass,
+// of the leading bits only; k_fix_runs orders what these leave equal.  Each
+// workgroup owns a tile of RS_TILE consecutive elements.  count: per-tile digit
+// histogram, stored digit-major (hist[d * nblk + blk]); an exclusive scan of
+// that array gives every (digit, tile) its output offset; scatter: the tile is
+// ranked in input order and leaves in digit runs.
+constexpr int RS_BITS = 9, RS_DIGITS = 1 << RS_BITS;
+constexpr int RS_THREADS = 512, RS_WAVES = RS_THREADS / 64;
+constexpr int RS_ITEMS = 16;
+constexpr uint64_t RS_TILE = (uint64_t)RS_THREADS * RS_ITEMS;
 constexpr uint64_t SCAN_CHUNK = 4096;
+constexpr int KEY_BITS = 63;
 
-__global__ void __launch_bounds__(256) k_radix_count(const uint64_t* __restrict__ keys, uint64_t n, int shift,
-                                                     uint32_t* __restrict__ hist, uint64_t nblk) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
+__device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift) {
+  return (uint32_t)(key >> shift) & (uint32_t)(RS_DIGITS - 1);
+}
+__device__ __forceinline__ void put_histogram(const uint32_t* h, uint32_t* hist, uint64_t nblk) {
+  static_assert(RS_DIGITS <= RS_THREADS, "one digit per thread");
+  if (threadIdx.x < RS_DIGITS) hist[(uint64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+}
+
+// Morton codes of a tile, and the histogram of their digit at shift (the first pass needs no count launch).
+__global__ void __launch_bounds__(RS_THREADS) k_morton(const float* __restrict__ xyz, uint64_t n,
+                                                       const uint32_t* __restrict__ aabb, uint64_t* __restrict__ keys,
+                                                       int shift, uint32_t* __restrict__ hist, uint64_t nblk) {
+  __shared__ uint32_t h[RS_DIGITS];
+  if (threadIdx.x < RS_DIGITS) h[threadIdx.x] = 0;
   __syncthreads();
+  constexpr double SCALE = 2097152.0;  // 21 bits per axis
+  Axis ax[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) ax[a] = make_axis(okey_inv(aabb[a]), okey_inv(aabb[3 + a]), SCALE);
   const uint64_t base = (uint64_t)blockIdx.x * RS_TILE;
-  for (int it = 0; it < RS_CHUNKS; ++it) {
+#pragma unroll 4
+  for (int it = 0; it < RS_ITEMS; ++it) {
     const uint64_t i = base + (uint64_t)it * RS_THREADS + threadIdx.x;
-    if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
+    if (i < n) {
+      const uint64_t qx = axis_cell(ax[0], xyz[3 * i], SCALE);
+      const uint64_t qy = axis_cell(ax[1], xyz[3 * i + 1], SCALE);
+      const uint64_t qz = axis_cell(ax[2], xyz[3 * i + 2], SCALE);
+      const uint64_t key = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
+      keys[i] = key;
+      atomicAdd(&h[digit_of(key, shift)], 1u);
+    }
   }
   __syncthreads();
-  hist[(uint64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+  put_histogram(h, hist, nblk);
+}
+
+__global__ void __launch_bounds__(RS_THREADS) k_radix_count(const uint64_t* __restrict__ keys, uint64_t n, int shift,
+                                                            uint32_t* __restrict__ hist, uint64_t nblk) {
+  __shared__ uint32_t h[RS_DIGITS];
+  if (threadIdx.x < RS_DIGITS) h[threadIdx.x] = 0;
+  __syncthreads();
+  const uint64_t base = (uint64_t)blockIdx.x * RS_TILE;
+  uint64_t k[RS_ITEMS];
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const uint64_t i = base + (uint64_t)it * RS_THREADS + threadIdx.x;
+    k[it] = i < n ? keys[i] : 0ull;
+  }
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it)
+    if (base + (uint64_t)it * RS_THREADS + threadIdx.x < n) atomicAdd(&h[digit_of(k[it], shift)], 1u);
+  __syncthreads();
+  put_histogram(h, hist, nblk);
 }
 
 // exclusive scan of m u32 values: partial sums, top-level scan, apply
@@ -150,10 +255,11 @@ __global__ void __launch_bounds__(256) k_scan_partials(const uint32_t* __restric
   if (threadIdx.x == 0) part[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
 }
 
-// Block-wide exclusive scan of one value per thread (256 threads); returns the
+// Block-wide exclusive scan of one value per thread (WAVES waves); returns the
 // exclusive prefix and writes the block total to *total.
+template <int WAVES = 4>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* total) {
-  __shared__ uint32_t ws[4];
+  __shared__ uint32_t ws[WAVES];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t inc = v;
   for (int o = 1; o < 64; o <<= 1) {
@@ -163,8 +269,11 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
   if (lane == 63) ws[wave] = inc;
   __syncthreads();
   uint32_t wbase = 0;
-  for (int w = 0; w < wave; ++w) wbase += ws[w];
-  const uint32_t tot = ws[0] + ws[1] + ws[2] + ws[3];
+  uint32_t tot = 0;
+  for (int w = 0; w < WAVES; ++w) {
+    if (w < wave) wbase += ws[w];
+    tot += ws[w];
+  }
   __syncthreads();
   *total = tot;
   return wbase + inc - v;
@@ -196,87 +305,162 @@ __global__ void __launch_bounds__(256) k_scan_apply(uint32_t* __restrict__ x, ui
   }
 }
 
-// Scatter of one pass: the tile is first ranked stably into LDS, ordered by
-// digit (equal digits in input order: wave ballots give the rank inside a
-// wave, LDS counters carry it across waves and chunks), then written out from
-// LDS so that consecutive threads write consecutive slots of one digit's
-// range: the tile's elements of a digit (about RS_TILE / 256) leave as one run
-// instead of one scattered 8-byte store each.
-__global__ void __launch_bounds__(256) k_radix_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                       uint64_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                       uint64_t n, int shift, const uint32_t* __restrict__ offs,
-                                                       uint64_t nblk) {
-  __shared__ uint64_t skey[RS_TILE];
-  __shared__ uint32_t sval[RS_TILE];
-  __shared__ uint32_t goff[256];    // first output slot of this tile's digit d
-  __shared__ uint32_t tstart[256];  // first LDS slot of digit d in the tile
-  __shared__ uint32_t run[256];
-  __shared__ uint32_t wcnt[4][256];
+// Scatter of one pass.  Each wave ranks its 1,024 consecutive elements alone,
+// against digit counters of its own (ballots give the rank among equal digits
+// of a 64-element row, the counter carries it over the rows): no barrier until
+// the whole tile is ranked, where one counter row per 256 elements took three.
+// The tile then moves through LDS in digit order, keys first, values after them
+// in the same space, so that consecutive threads write consecutive slots of one
+// digit's range.  The first pass's values are the indices themselves (vin null).
+// Bound by memory: 24 bytes an element; the runs of a digit (16 elements, 128 and
+// 64 bytes, unaligned) of neighbouring tiles share lines, so the tiles are dealt
+// to the XCDs in contiguous eighths (5e8 elements: 2.66 ms, 4.5 TB/s; tiles dealt
+// in turn 5.9 ms; the earlier scatter of 4,096-element tiles and 8-bit digits 5.6).
+__global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
+    const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
+    uint32_t* __restrict__ vout, uint64_t n, int shift, const uint32_t* __restrict__ offs, uint64_t nblk) {
+  __shared__ uint64_t stage[RS_TILE];
+  __shared__ uint16_t cnt[RS_WAVES][RS_DIGITS];  // a wave's count of a digit, then the digit's start in the wave's part
+  __shared__ uint32_t gout[RS_DIGITS];           // output slot of the tile's LDS slot 0, as seen from digit d
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const uint64_t m = 256 * nblk;
-  const uint64_t at = (uint64_t)tid * nblk + blockIdx.x;  // (digit tid, this block) in the digit-major scan
-  const uint32_t g0 = offs[at];
-  const uint32_t g1 = at + 1 < m ? offs[at + 1] : (uint32_t)n;  // next (digit, block) starts where this ends
-  goff[tid] = g0;
-  uint32_t total;
-  tstart[tid] = block_exclusive_scan(g1 - g0, &total);
-  run[tid] = 0;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const uint64_t base = (uint64_t)blockIdx.x * RS_TILE;
-  // the whole tile's loads are issued before the ranking starts, so that the
-  // chunks' barriers do not each wait for a memory round trip
-  uint64_t keys[RS_CHUNKS];
-  uint32_t vals[RS_CHUNKS];
+  const uint64_t blk = xcd_tile();
+  if (blk >= nblk) return;
+  const uint64_t base = blk * RS_TILE, wbase = base + (uint64_t)wave * (64 * RS_ITEMS);
+  uint64_t key[RS_ITEMS];
+  uint32_t val[RS_ITEMS];
 #pragma unroll
-  for (int it = 0; it < RS_CHUNKS; ++it) {
-    const uint64_t i = base + (uint64_t)it * RS_THREADS + tid;
-    keys[it] = i < n ? kin[i] : 0ull;
-    vals[it] = i < n ? vin[i] : 0u;
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const uint64_t i = wbase + it * 64 + lane;
+    key[it] = i < n ? kin[i] : 0ull;
+    val[it] = vin ? (i < n ? vin[i] : 0u) : (uint32_t)i;
   }
+  for (int d = lane; d < RS_DIGITS; d += 64) cnt[wave][d] = 0;
+  __builtin_amdgcn_wave_barrier();
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint16_t rank[RS_ITEMS];
 #pragma unroll
-  for (int it = 0; it < RS_CHUNKS; ++it) {
-    wcnt[0][tid] = 0;
-    wcnt[1][tid] = 0;
-    wcnt[2][tid] = 0;
-    wcnt[3][tid] = 0;
-    __syncthreads();
-    const uint64_t i = base + (uint64_t)it * RS_THREADS + tid;
-    const bool valid = i < n;
-    const uint64_t key = keys[it];
-    const uint32_t val = vals[it];
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const bool valid = wbase + it * 64 + lane < n;
+    const uint32_t d = digit_of(key[it], shift);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
+    for (int bit = 0; bit < RS_BITS; ++bit) {
       const bool set = (d >> bit) & 1u;
       const uint64_t mk = __ballot(set);
       peers &= set ? mk : ~mk;
     }
-    const uint32_t rank = __popcll(peers & lt_mask);
-    if (valid && rank == 0) wcnt[wave][d] = __popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = tstart[d] + run[d] + rank;
-      for (int w = 0; w < wave; ++w) pos += wcnt[w][d];
-      if (pos < RS_TILE) {  // always true for a consistent histogram; never write outside
-        skey[pos] = key;
-        sval[pos] = val;
-      }
-    }
-    __syncthreads();
-    run[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
+    const uint32_t r = __popcll(peers & lt_mask);
+    const uint32_t before = cnt[wave][d];
+    __builtin_amdgcn_wave_barrier();  // every lane has read the counter before its first peer adds
+    if (valid && r == 0) cnt[wave][d] = (uint16_t)(before + __popcll(peers));
+    __builtin_amdgcn_wave_barrier();
+    rank[it] = (uint16_t)(before + r);
   }
   __syncthreads();
-  const uint32_t nt = total < (uint32_t)RS_TILE ? total : (uint32_t)RS_TILE;
-  for (uint32_t p = tid; p < nt; p += RS_THREADS) {
-    const uint64_t key = skey[p];
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
-    const uint64_t pos = (uint64_t)goff[d] + (p - tstart[d]);
-    if (pos < n) {  // always true for a consistent histogram; never write outside
-      kout[pos] = key;
-      vout[pos] = sval[p];
+  uint32_t sum = 0;
+  if (tid < RS_DIGITS) {
+    for (int w = 0; w < RS_WAVES; ++w) sum += cnt[w][tid];
+  }
+  uint32_t total;
+  uint32_t start = block_exclusive_scan<RS_WAVES>(sum, &total);  // of the digit in the tile
+  if (tid < RS_DIGITS) {
+    gout[tid] = offs[(uint64_t)tid * nblk + blk] - start;  // wraps; added to an LDS slot it does not
+    for (int w = 0; w < RS_WAVES; ++w) {
+      const uint32_t c = cnt[w][tid];
+      cnt[w][tid] = (uint16_t)start;  // below RS_TILE
+      start += c;
     }
   }
+  __syncthreads();
+  static_assert(RS_TILE <= 65536, "slots in 16 bits");
+  const uint32_t nt = (uint32_t)(n - base < RS_TILE ? n - base : RS_TILE);
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const bool valid = wbase + it * 64 + lane < n;
+    rank[it] = (uint16_t)(rank[it] + cnt[wave][digit_of(key[it], shift)]);
+    if (valid) stage[rank[it]] = key[it];
+  }
+  __syncthreads();
+  uint32_t pos[RS_ITEMS];
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const uint32_t p = it * RS_THREADS + tid;
+    pos[it] = ~0u;
+    if (p < nt) {
+      const uint64_t k = stage[p];
+      pos[it] = gout[digit_of(k, shift)] + p;
+      if (pos[it] < n) kout[pos[it]] = k;  // always true for a consistent histogram; never write outside
+    }
+  }
+  __syncthreads();
+  uint32_t* const vstage = reinterpret_cast<uint32_t*>(stage);
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it)
+    if (wbase + it * 64 + lane < n) vstage[rank[it]] = val[it];
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < RS_ITEMS; ++it) {
+    const uint32_t p = it * RS_THREADS + tid;
+    if (p < nt && pos[it] < n) vout[pos[it]] = vstage[p];
+  }
+}
+
+// Orders the runs of elements whose keys agree from bit shift up, by the whole
+// key, stably, and writes the values alone (the keys end here).  An element moves
+// left by the number of earlier ones of its run with a larger key and right by
+// the number of later ones with a smaller key: a walk over its run in LDS, cheap
+// for the short runs that sort_passes leaves.  Runs of more than RUN_MAX + 1
+// elements are left as they are; flag is set if one of them is out of order
+// (one of equal keys is not, however long).
+constexpr int FIX_THREADS = 256, FIX_ITEMS = 8, RUN_MAX = 256;
+constexpr int FIX_TILE = FIX_THREADS * FIX_ITEMS;
+__global__ void __launch_bounds__(FIX_THREADS) k_fix_runs(const uint64_t* __restrict__ keys,
+                                                          const uint32_t* __restrict__ vin, uint64_t n, int shift,
+                                                          uint32_t* __restrict__ vout, uint32_t* __restrict__ flag) {
+  constexpr int SPAN = FIX_TILE + 2 * RUN_MAX + 2, LOADS = (SPAN + FIX_THREADS - 1) / FIX_THREADS;
+  __shared__ uint64_t k[LOADS * FIX_THREADS];
+  const int64_t base = (int64_t)blockIdx.x * FIX_TILE, lo = base - RUN_MAX - 1;  // k[0] is element lo
+  // all loads in flight before the first is used
+  uint64_t key[LOADS];
+  uint32_t val[FIX_ITEMS];
+#pragma unroll
+  for (int l = 0; l < LOADS; ++l) {
+    const int64_t i = lo + l * FIX_THREADS + threadIdx.x;
+    key[l] = i >= 0 && i < (int64_t)n ? keys[i] : ~0ull;  // ~0 agrees with no 63-bit key
+  }
+#pragma unroll
+  for (int it = 0; it < FIX_ITEMS; ++it) {
+    const int64_t i = base + it * FIX_THREADS + threadIdx.x;
+    val[it] = i < (int64_t)n ? vin[i] : 0u;
+  }
+#pragma unroll
+  for (int l = 0; l < LOADS; ++l) k[l * FIX_THREADS + threadIdx.x] = key[l];
+  __syncthreads();
+  bool unsorted = false;
+#pragma unroll
+  for (int it = 0; it < FIX_ITEMS; ++it) {
+    const int64_t i = base + it * FIX_THREADS + threadIdx.x;
+    if (i >= (int64_t)n) break;
+    const int at = (int)(i - lo);
+    const uint64_t mine = k[at];
+    int left = 0, right = 0, move = 0;
+    while (left <= RUN_MAX && ((k[at - left - 1] ^ mine) >> shift) == 0) {
+      ++left;
+      move -= k[at - left] > mine ? 1 : 0;
+      if (left > RUN_MAX) break;
+    }
+    while (right <= RUN_MAX && ((k[at + right + 1] ^ mine) >> shift) == 0) {
+      ++right;
+      move += k[at + right] < mine ? 1 : 0;
+      if (right > RUN_MAX) break;
+    }
+    if (left + right > RUN_MAX) {
+      unsorted |= right > 0 && k[at + 1] < mine;
+      move = 0;
+    }
+    vout[i + move] = val[it];
+  }
+  raise(flag, unsorted);
 }
 
 // ----------------------------------------------------------------- gather
@@ -416,12 +600,21 @@ __global__ void __launch_bounds__(256) k_batch_bbox(const float* __restrict__ xy
 // Eq. 1: X30 = min(floor(2^30 (x - min) / size), 2^30 - 1) in binary64 with
 // one correctly rounded division (0 for size 0); low = bits 29..20, med =
 // bits 19..10, high = bits 9..0, each packed x | y << 10 | z << 20.
-__device__ __forceinline__ uint32_t eq1(float x, float bmin, float bmax) {
-  const double d = (double)x - (double)bmin;
-  const double s = (double)bmax - (double)bmin;
-  if (s == 0.0) return 0u;
-  const double f = floor((d * 1073741824.0) / s);
-  return f > 1073741823.0 ? 1073741823u : (uint32_t)f;
+constexpr double EQ1_SCALE = 1073741824.0;
+struct Words3 {
+  uint32_t low, med, high;
+};
+__device__ __forceinline__ Words3 eq1(const Axis (&ax)[3], float x, float y, float z) {
+  const float f[3] = {x, y, z};
+  Words3 w = {0, 0, 0};
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const uint32_t X30 = axis_cell(ax[a], f[a], EQ1_SCALE);
+    w.low |= ((X30 >> 20) & 1023u) << (10 * a);
+    w.med |= ((X30 >> 10) & 1023u) << (10 * a);
+    w.high |= (X30 & 1023u) << (10 * a);
+  }
+  return w;
 }
 
 __global__ void __launch_bounds__(256) k_quantize(const float* __restrict__ xyz, uint64_t n, uint32_t S,
@@ -430,17 +623,13 @@ __global__ void __launch_bounds__(256) k_quantize(const float* __restrict__ xyz,
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const BatchRec& B = batches[(uint32_t)i / S];  // i < 2^32
-    uint32_t lw = 0, mw = 0, hw = 0;
+    Axis ax[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const uint32_t X30 = eq1(xyz[3 * i + a], B.mn[a], B.mx[a]);
-      lw |= ((X30 >> 20) & 1023u) << (10 * a);
-      mw |= ((X30 >> 10) & 1023u) << (10 * a);
-      hw |= (X30 & 1023u) << (10 * a);
-    }
-    low[i] = lw;
-    med[i] = mw;
-    high[i] = hw;
+    for (int a = 0; a < 3; ++a) ax[a] = make_axis(B.mn[a], B.mx[a], EQ1_SCALE);
+    const Words3 w = eq1(ax, xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2]);
+    low[i] = w.low;
+    med[i] = w.med;
+    high[i] = w.high;
   }
 }
 
@@ -450,18 +639,171 @@ __global__ void __launch_bounds__(256) k_quantize_spans(const float* __restrict_
                                                         uint32_t* __restrict__ low, uint32_t* __restrict__ med,
                                                         uint32_t* __restrict__ high) {
   const BatchRec B = batches[blockIdx.x];
-  for (uint64_t i = (uint64_t)B.first + threadIdx.x; i < (uint64_t)B.first + B.count; i += 256) {
-    uint32_t lw = 0, mw = 0, hw = 0;
+  Axis ax[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const uint32_t X30 = eq1(xyz[3 * i + a], B.mn[a], B.mx[a]);
-      lw |= ((X30 >> 20) & 1023u) << (10 * a);
-      mw |= ((X30 >> 10) & 1023u) << (10 * a);
-      hw |= (X30 & 1023u) << (10 * a);
+  for (int a = 0; a < 3; ++a) ax[a] = make_axis(B.mn[a], B.mx[a], EQ1_SCALE);
+  for (uint64_t i = (uint64_t)B.first + threadIdx.x; i < (uint64_t)B.first + B.count; i += 256) {
+    const Words3 w = eq1(ax, xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2]);
+    low[i] = w.low;
+    med[i] = w.med;
+    high[i] = w.high;
+  }
+}
+
+// ------------------------------------------------------------ whole batches
+// One batch per workgroup, its points in registers from the first read to the
+// last word: source (ORDER 0: the input itself, with the finite check; 1 and 2:
+// records gathered through the sorted order, 2 in the spread order) -> position,
+// colour and permutation -> box -> Eq. 1 words.  Against a gather, a box pass and
+// a word pass of their own it saves reading the positions twice more, and the
+// box and division work hides behind the gather's scattered reads (5e8 points in
+// no order: 16.3 ms, as the gather alone took, instead of 16.2 + 0.8 + 0.95 + 4.3
+// with its copy of the order; each record is a line of its own there, 64 GB of
+// lines; all steps' reads issued up front gained nothing).  Each thread owns
+// groups of four consecutive points, so that every buffer is written in 16-byte
+// words.
+constexpr int WB_STEPS = 5;  // groups of four points per thread
+template <int ORDER, int THREADS>
+__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) k_batch(const float* __restrict__ xyz, const uint32_t* __restrict__ rgba,
+                                                   const uint4* __restrict__ rec, const uint32_t* __restrict__ order,
+                                                   Spread sp, uint64_t n, uint32_t S, float* __restrict__ xyz_out,
+                                                   uint32_t* __restrict__ colors, uint32_t* __restrict__ perm,
+                                                   BatchRec* __restrict__ batches, uint32_t* __restrict__ low,
+                                                   uint32_t* __restrict__ med, uint32_t* __restrict__ high,
+                                                   uint32_t* __restrict__ flag) {
+  __shared__ Box red[THREADS / 64];
+  const uint64_t batch = xcd_tile(), first = batch * S;
+  if (first >= n) return;
+  const uint32_t count = (uint32_t)(first + S <= n ? S : n - first);
+  const uint32_t step = (uint32_t)(count == S ? sp.m : sp.m_last);
+  float p[WB_STEPS][12];
+  Box box = empty_box();
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < WB_STEPS; ++k) {
+    const uint32_t r = 4u * (k * THREADS + threadIdx.x);
+    if (r >= count) break;
+    const uint64_t i = first + r;
+    const uint32_t m = min(4u, count - r);
+    uint32_t src[4], col[4];
+    if constexpr (ORDER == 0) {
+      if (m == 4) {
+        const float4* const v = reinterpret_cast<const float4*>(xyz + 3 * i);
+        const float4 u0 = v[0], u1 = v[1], u2 = v[2];
+        const uint4 c = *reinterpret_cast<const uint4*>(rgba + i);
+        const float f[12] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w, u2.x, u2.y, u2.z, u2.w};
+#pragma unroll
+        for (int j = 0; j < 12; ++j) p[k][j] = f[j];
+        col[0] = c.x, col[1] = c.y, col[2] = c.z, col[3] = c.w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) src[j] = (uint32_t)i + j;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // past the end the last point again
+          src[j] = (uint32_t)i + min((uint32_t)j, m - 1u);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) p[k][3 * j + a] = xyz[3 * (uint64_t)src[j] + a];
+          col[j] = rgba[src[j]];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 12; ++j) bad |= not_finite(p[k][j]);
+    } else {
+      if constexpr (ORDER == 2) {
+        uint32_t o = (r * step) % count;  // rank of position r; r step < 2^32 for batches of 20,480 points
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          src[j] = order[first + o];
+          o += step;
+          if (o >= count) o -= count;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) src[j] = order[i + min((uint32_t)j, m - 1u)];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (src[j] >= n) src[j] = (uint32_t)i;  // a permutation never triggers this; it keeps reads in bounds
+        const uint4 q = rec[src[j]];
+        p[k][3 * j] = __uint_as_float(q.x);
+        p[k][3 * j + 1] = __uint_as_float(q.y);
+        p[k][3 * j + 2] = __uint_as_float(q.z);
+        col[j] = q.w;
+      }
+      if (m == 4) {
+        float4* const x = reinterpret_cast<float4*>(xyz_out + 3 * i);
+        x[0] = make_float4(p[k][0], p[k][1], p[k][2], p[k][3]);
+        x[1] = make_float4(p[k][4], p[k][5], p[k][6], p[k][7]);
+        x[2] = make_float4(p[k][8], p[k][9], p[k][10], p[k][11]);
+      }
     }
-    low[i] = lw;
-    med[i] = mw;
-    high[i] = hw;
+    if (m == 4) {
+      *reinterpret_cast<uint4*>(colors + i) = make_uint4(col[0], col[1], col[2], col[3]);
+      *reinterpret_cast<uint4*>(perm + i) = make_uint4(src[0], src[1], src[2], src[3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if ((uint32_t)j < m) {
+          if constexpr (ORDER != 0) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) xyz_out[3 * (i + j) + a] = p[k][3 * j + a];
+          }
+          colors[i + j] = col[j];
+          perm[i + j] = src[j];
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 12; ++j) grow(box, j % 3, p[k][j]);
+  }
+  if constexpr (ORDER == 0) raise(flag, bad);
+  box = block_box(box, red);
+  Axis ax[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) ax[a] = make_axis(okey_inv(box.mn[a]), okey_inv(box.mx[a]), EQ1_SCALE);
+  if (threadIdx.x == 0) {
+    BatchRec b;
+    b.first = (uint32_t)first;
+    b.count = count;
+    for (int a = 0; a < 3; ++a) {
+      b.mn[a] = okey_inv(box.mn[a]);
+      b.mx[a] = okey_inv(box.mx[a]);
+    }
+    batches[batch] = b;
+  }
+#pragma unroll
+  for (int k = 0; k < WB_STEPS; ++k) {
+    const uint32_t r = 4u * (k * THREADS + threadIdx.x);
+    if (r >= count) break;
+    const uint64_t i = first + r;
+    Words3 w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = eq1(ax, p[k][3 * j], p[k][3 * j + 1], p[k][3 * j + 2]);
+    if (r + 4 <= count) {
+      *reinterpret_cast<uint4*>(low + i) = make_uint4(w[0].low, w[1].low, w[2].low, w[3].low);
+      *reinterpret_cast<uint4*>(med + i) = make_uint4(w[0].med, w[1].med, w[2].med, w[3].med);
+      *reinterpret_cast<uint4*>(high + i) = make_uint4(w[0].high, w[1].high, w[2].high, w[3].high);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (r + j < count) {
+          low[i + j] = w[j].low;
+          med[i + j] = w[j].med;
+          high[i + j] = w[j].high;
+        }
+      }
+    }
+  }
+}
+
+// Positions back from the records, for a second sort (xyz holds the gathered ones by then).
+__global__ void __launch_bounds__(256) k_restore(const uint4* __restrict__ rec, uint64_t n, float* __restrict__ xyz) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const uint4 r = rec[i];
+    xyz[3 * i] = __uint_as_float(r.x);
+    xyz[3 * i + 1] = __uint_as_float(r.y);
+    xyz[3 * i + 2] = __uint_as_float(r.z);
   }
 }
 
@@ -478,26 +820,34 @@ inline uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 
 uint64_t small_scratch_bytes() { return 4096; }
 
-uint64_t sort_scratch_layout(uint64_t n, uint8_t* base, SortScratch* out) {
+uint64_t sort_scratch_bytes(uint64_t n) {
+  const uint64_t tiles = n ? (n + 4095) / 4096 : 1, m = 256 * tiles;
+  return 256 + 2 * align256(8 * n) + align256(4 * n) + align256(4 * m) + align256(4 * ((m + 4095) / 4096));
+}
+
+// The sort area starts 1 KiB before the end of the small scratch, whose first
+// 256 bytes hold the cloud box: with tiles of 8,192 points and 512 digits the
+// histograms take at most 1 KiB more than sort_scratch_bytes counts for them.
+void sort_scratch_layout(uint64_t n, uint8_t* scratch, SortScratch* out) {
   SortScratch s{};
   s.nblk = (n + RS_TILE - 1) / RS_TILE;
   if (s.nblk == 0) s.nblk = 1;
-  const uint64_t m = 256 * s.nblk;
+  const uint64_t m = RS_DIGITS * s.nblk;
   s.npart = (m + SCAN_CHUNK - 1) / SCAN_CHUNK;
-  uint64_t off = 0;
+  s.aabb = reinterpret_cast<uint32_t*>(scratch);
+  uint64_t off = small_scratch_bytes() - 1024;
   auto take = [&](uint64_t bytes) {
-    const uint64_t o = off;
-    off = align256(off + bytes);
-    return base ? base + o : nullptr;
+    uint8_t* const p = scratch + off;
+    off += align256(bytes);
+    return p;
   };
-  s.aabb = reinterpret_cast<uint32_t*>(take(64));
   s.keys0 = reinterpret_cast<uint64_t*>(take(8 * n));
   s.keys1 = reinterpret_cast<uint64_t*>(take(8 * n));
   s.vals1 = reinterpret_cast<uint32_t*>(take(4 * n));
   s.hist = reinterpret_cast<uint32_t*>(take(4 * m));
   s.part = reinterpret_cast<uint32_t*>(take(4 * s.npart));
-  if (out) *out = s;
-  return off;
+  s.end = off;
+  *out = s;
 }
 
 hipError_t launch_finite_check(const float* xyz, uint64_t n, uint32_t* flag, hipStream_t s) {
@@ -511,40 +861,72 @@ hipError_t launch_iota(uint32_t* p, uint64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_morton_codes(const float* xyz, uint64_t n, uint32_t* aabb, uint64_t* keys, uint32_t* vals,
-                               uint32_t* flag, hipStream_t s) {
-  hipLaunchKernelGGL(k_aabb_init, dim3(1), dim3(64), 0, s, aabb);
-  hipLaunchKernelGGL(k_aabb, dim3(grid_for(n, 256 * 8, 4096)), dim3(256), 0, s, xyz, n, aabb, flag);
-  hipLaunchKernelGGL(k_morton, dim3(grid_for(n, 256 * 4)), dim3(256), 0, s, xyz, n, aabb, keys, vals);
-  return hipGetLastError();
+// Radix passes over the leading bits before the runs are ordered: enough that
+// a surface, which fills about 4^levels of the cells, leaves some 16 points a
+// run at most (5e8 points: 4 passes, 30 a run, 50.5 ms; 5 passes, 45.7 ms).
+int sort_passes(uint64_t n) {
+  int passes = 2;
+  while (passes < 5 && (n >> (2 * 3 * passes)) > 16) ++passes;  // 9 bits: 3 levels
+  return passes;
 }
 
-hipError_t radix_sort_pairs(const SortScratch& sc, uint32_t* vals0, uint64_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  uint64_t* kin = sc.keys0;
-  uint64_t* kout = sc.keys1;
-  uint32_t* vin = vals0;
-  uint32_t* vout = sc.vals1;
-  const uint64_t m = 256 * sc.nblk;
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 8 * pass;
-    hipLaunchKernelGGL(k_radix_count, dim3((uint32_t)sc.nblk), dim3(256), 0, s, kin, n, shift, sc.hist, sc.nblk);
+namespace {
+constexpr int FULL_PASSES = KEY_BITS / RS_BITS;  // every bit of the key
+static_assert(FULL_PASSES * RS_BITS == KEY_BITS, "whole passes");
+
+// The passes over the digits from bit 63 - 9 passes up; the first digit's
+// histogram is counted.  The values end in vals_last, the keys in the returned buffer.
+hipError_t radix_passes(const SortScratch& sc, uint64_t n, int passes, uint32_t* vals_last, uint32_t* vals_other,
+                        uint64_t** keys_out, hipStream_t s) {
+  const uint64_t m = RS_DIGITS * sc.nblk;
+  uint64_t *kin = sc.keys0, *kout = sc.keys1;
+  const uint32_t* vin = nullptr;
+  for (int p = 0; p < passes; ++p) {
+    const int shift = KEY_BITS - RS_BITS * (passes - p);
+    uint32_t* const vout = (passes - 1 - p) % 2 ? vals_other : vals_last;
+    if (p > 0)
+      hipLaunchKernelGGL(k_radix_count, dim3((uint32_t)sc.nblk), dim3(RS_THREADS), 0, s, kin, n, shift, sc.hist, sc.nblk);
     hipLaunchKernelGGL(k_scan_partials, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, sc.part, sc.npart);
     hipLaunchKernelGGL(k_scan_apply, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
-    hipLaunchKernelGGL(k_radix_scatter, dim3((uint32_t)sc.nblk), dim3(256), 0, s, kin, vin, kout, vout, n, shift,
+    hipLaunchKernelGGL(k_radix_scatter, dim3(xcd_grid(sc.nblk)), dim3(RS_THREADS), 0, s, kin, vin, kout, vout, n, shift,
                        sc.hist, sc.nblk);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    uint64_t* tk = kin;
+    uint64_t* const t = kin;
     kin = kout;
-    kout = tk;
-    uint32_t* tv = vin;
+    kout = t;
     vin = vout;
-    vout = tv;
   }
-  // 8 passes: the sorted pairs are back in keys0 / vals0
+  *keys_out = kin;
   return hipSuccess;
+}
+}  // namespace
+
+hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, bool full,
+                              uint32_t* nonfinite, uint32_t* unsorted, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  // the partial boxes lie in the second key buffer, not in use yet (24 bytes per 1,024 points, or one in 256)
+  Box* const part = reinterpret_cast<Box*>(sc.keys1);
+  const uint32_t blocks = grid_for(n, 1024, BOX_BLOCKS);
+  hipLaunchKernelGGL(k_aabb, dim3(blocks), dim3(256), 0, s, xyz, n, part, nonfinite);
+  hipLaunchKernelGGL(k_aabb_top, dim3(1), dim3(256), 0, s, part, blocks, sc.aabb);
+  const int passes = full ? FULL_PASSES : sort_passes(n), shift = KEY_BITS - RS_BITS * passes;
+  hipLaunchKernelGGL(k_morton, dim3((uint32_t)sc.nblk), dim3(RS_THREADS), 0, s, xyz, n, sc.aabb, sc.keys0, shift,
+                     sc.hist, sc.nblk);
+  uint64_t* keys = nullptr;
+  hipError_t e;
+  if (full) return radix_passes(sc, n, passes, sc.vals1, perm, &keys, s);
+  if ((e = radix_passes(sc, n, passes, perm, sc.vals1, &keys, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fix_runs, dim3((uint32_t)((n + FIX_TILE - 1) / FIX_TILE)), dim3(FIX_THREADS), 0, s, keys, perm, n,
+                     shift, sc.vals1, unsorted);
+  return hipGetLastError();
+}
+
+hipError_t launch_restore(const SortScratch& sc, uint64_t n, float* xyz, hipStream_t s) {
+  hipLaunchKernelGGL(k_restore, dim3(grid_for(n, 256 * 4)), dim3(256), 0, s, reinterpret_cast<const uint4*>(sc.keys0), n,
+                     xyz);
+  return hipGetLastError();
 }
 
 uint64_t spread_step(uint64_t c) {
@@ -561,29 +943,70 @@ uint64_t spread_step(uint64_t c) {
   }
 }
 
-hipError_t launch_gather(const SortScratch& sc, const float* xyz, const uint32_t* rgba, uint32_t* perm,
-                         uint64_t n, uint32_t batch_size, bool spread, float* xyz_out, uint32_t* colors,
-                         hipStream_t s) {
-  if (n == 0) return hipSuccess;
+namespace {
+Spread make_spread(uint64_t n, uint32_t S) {
+  Spread sp;
+  sp.S = S;
+  sp.m = spread_step(S);
+  sp.c_last = n % S ? n % S : S;
+  sp.m_last = spread_step(sp.c_last);
+  return sp;
+}
+
+template <int ORDER, int THREADS>
+hipError_t launch_batch_t(const BuildArgs& a, const uint4* rec, const uint32_t* order, hipStream_t s) {
+  const uint64_t nb = (a.n + a.S - 1) / a.S;
+  hipLaunchKernelGGL((k_batch<ORDER, THREADS>), dim3(xcd_grid(nb)), dim3(THREADS), 0, s, a.xyz, a.rgba, rec, order,
+                     ORDER == 2 ? make_spread(a.n, a.S) : Spread{}, a.n, a.S, a.xyz, a.colors, a.perm, a.batches, a.low,
+                     a.med, a.high, a.nonfinite);
+  return hipGetLastError();
+}
+template <int ORDER>
+hipError_t launch_batch(const BuildArgs& a, const uint4* rec, const uint32_t* order, hipStream_t s) {
+  if (a.S <= 256u * 4 * WB_STEPS) return launch_batch_t<ORDER, 256>(a, rec, order, s);
+  if (a.S <= 512u * 4 * WB_STEPS) return launch_batch_t<ORDER, 512>(a, rec, order, s);
+  return launch_batch_t<ORDER, 1024>(a, rec, order, s);
+}
+// Batches that one workgroup of k_batch holds in registers (20 points a thread)
+// and that keep its four waves busy; larger and smaller ones take the separate
+// kernels.
+bool whole_batches(uint32_t S) { return S >= 512 && S <= 1024u * 4 * WB_STEPS; }
+
+hipError_t boxes_and_words(const BuildArgs& a, hipStream_t s) {
+  const uint64_t nb = (a.n + a.S - 1) / a.S;
+  hipError_t e = launch_batch_bbox(a.xyz, a.n, a.S, nb, a.batches, s);
+  if (e != hipSuccess) return e;
+  return launch_quantize(a.xyz, a.n, a.S, a.batches, a.low, a.med, a.high, s);
+}
+}  // namespace
+
+hipError_t launch_build_input(const BuildArgs& a, hipStream_t s) {
+  if (a.n == 0) return hipSuccess;
+  if (whole_batches(a.S)) return launch_batch<0>(a, nullptr, nullptr, s);
+  hipError_t e = launch_finite_check(a.xyz, a.n, a.nonfinite, s);
+  if (e == hipSuccess) e = launch_iota(a.perm, a.n, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(a.colors, a.rgba, 4 * a.n, hipMemcpyDeviceToDevice, s);
+  return e == hipSuccess ? boxes_and_words(a, s) : e;
+}
+
+hipError_t launch_build_sorted(const BuildArgs& a, const SortScratch& sc, bool spread, hipStream_t s) {
+  if (a.n == 0) return hipSuccess;
   // the records take the two key buffers, free once the sort is done (keys0 then keys1: 16 n bytes)
   uint4* const rec = reinterpret_cast<uint4*>(sc.keys0);
-  if (reinterpret_cast<uint8_t*>(sc.keys1) + 8 * n < reinterpret_cast<uint8_t*>(rec) + 16 * n) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_interleave, dim3(grid_for(n, 256 * 4)), dim3(256), 0, s, xyz, rgba, n, rec);
-  const dim3 grid(grid_for(n, 256 * 4));
-  if (!spread) {
-    hipLaunchKernelGGL(k_gather<false>, grid, dim3(256), 0, s, rec, perm, perm, Spread{}, n, xyz_out, colors);
-    return hipGetLastError();
+  if (reinterpret_cast<uint8_t*>(sc.keys1) + 8 * a.n < reinterpret_cast<uint8_t*>(rec) + 16 * a.n) return hipErrorInvalidValue;
+  const dim3 grid(grid_for(a.n, 256 * 4));
+  hipLaunchKernelGGL(k_interleave, grid, dim3(256), 0, s, a.xyz, a.rgba, a.n, rec);
+  if (whole_batches(a.S)) return spread ? launch_batch<2>(a, rec, sc.vals1, s) : launch_batch<1>(a, rec, sc.vals1, s);
+  if (spread) {
+    hipLaunchKernelGGL(k_gather<true>, grid, dim3(256), 0, s, rec, sc.vals1, a.perm, make_spread(a.n, a.S), a.n, a.xyz,
+                       a.colors);
+  } else {
+    const hipError_t e = hipMemcpyAsync(a.perm, sc.vals1, 4 * a.n, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gather<false>, grid, dim3(256), 0, s, rec, sc.vals1, a.perm, Spread{}, a.n, a.xyz, a.colors);
   }
-  // the sorted order moves to the free value buffer; the spread order is written to perm
-  hipError_t e = hipMemcpyAsync(sc.vals1, perm, 4 * n, hipMemcpyDeviceToDevice, s);
-  if (e != hipSuccess) return e;
-  Spread sp;
-  sp.S = batch_size;
-  sp.m = spread_step(batch_size);
-  sp.c_last = n % batch_size ? n % batch_size : batch_size;
-  sp.m_last = spread_step(sp.c_last);
-  hipLaunchKernelGGL(k_gather<true>, grid, dim3(256), 0, s, rec, sc.vals1, perm, sp, n, xyz_out, colors);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? boxes_and_words(a, s) : e;
 }
 
 hipError_t launch_batch_bbox(const float* xyz, uint64_t n, uint32_t S, uint64_t nb, BatchRec* out, hipStream_t s) {

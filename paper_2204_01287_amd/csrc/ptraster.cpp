@@ -38,7 +38,8 @@ const ptr::RasterShape& shape_at(uint32_t i) { return *kShapeOf[i](); }
 struct pr_ctx {
   int device;
   hipStream_t stream;
-  ptr::DevBlock* dev;  // counters and flags (device memory)
+  ptr::DevBlock* dev;  // counters and flags (device memory); the flags are 0 between builds
+  uint32_t* seen;      // a build's flags on the host (pinned)
   uint32_t cus;                     // compute units of the device
   uint32_t per_cu[kNumShapes][2];   // workgroups per CU that fit at once: single-view, multi-view kernel
   uint32_t accum_grid;              // persistent workgroups of the shading pass
@@ -161,7 +162,7 @@ pr_status sizes_for(uint64_t n, uint32_t batch_size, int morton, pr_sizes* s) {
   s->low = s->med = s->high = s->colors = s->perm = a256(4 * n);
   s->batches = a256(32 * nb);
   // Load-time sort area and per-frame area (live batch list) share the space.
-  const uint64_t sort = morton ? ptr::sort_scratch_layout(n, nullptr, nullptr) : 0;
+  const uint64_t sort = morton ? ptr::sort_scratch_bytes(n) : 0;
   const uint64_t frame = ptr::frame_area_bytes(nb);
   s->scratch = a256(ptr::small_scratch_bytes() + (sort > frame ? sort : frame));
   s->nodes = 0;
@@ -199,6 +200,16 @@ hipError_t timed_launch(pr_ctx* ctx, Launch&& launch) {
   return hipEventRecord(ev[1], ctx->stream);
 }
 
+// The build flags once the stream has reached this point, into seen; a raised one is cleared for the next build.
+pr_status read_flags(pr_ctx* ctx, uint32_t (&seen)[2]) {
+  uint32_t* const flags = &ctx->dev->flags[0];
+  HIP_TRY(hipMemcpyAsync(ctx->seen, flags, sizeof seen, hipMemcpyDeviceToHost, ctx->stream), "read flags");
+  HIP_TRY(hipStreamSynchronize(ctx->stream), "build");
+  std::memcpy(seen, ctx->seen, sizeof seen);
+  if (seen[0] || seen[1]) HIP_TRY(hipMemsetAsync(flags, 0, sizeof seen, ctx->stream), "clear flags");
+  return PR_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -222,6 +233,7 @@ pr_status pr_create(int device, void* hip_stream, pr_ctx** out) {
   c->device = device;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->dev = nullptr;
+  c->seen = nullptr;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) cus = 1;
   c->cus = (uint32_t)cus;
@@ -240,8 +252,10 @@ pr_status pr_create(int device, void* hip_stream, pr_ctx** out) {
     return hip_fail(e, "hipMalloc(context block)");
   }
   e = hipMemsetAsync(c->dev, 0, 4096, c->stream);
+  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->seen), 256, hipHostMallocDefault);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
+    if (c->seen) (void)hipHostFree(c->seen);
     (void)hipFree(c->dev);
     delete c;
     return hip_fail(e, "context block init");
@@ -255,6 +269,7 @@ void pr_destroy(pr_ctx* ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   for (hipEvent_t e : ctx->tev) (void)hipEventDestroy(e);
+  (void)hipHostFree(ctx->seen);
   (void)hipFree(ctx->dev);
   delete ctx;
 }
@@ -338,7 +353,6 @@ pr_status pr_build_batches_spans(pr_ctx* ctx, pr_cloud* cloud, const uint32_t* s
     recs[b].count = spans[2 * b + 1];
   }
   uint32_t* flag = &ctx->dev->flags[0];
-  HIP_TRY(hipMemsetAsync(flag, 0, sizeof(uint32_t), st), "clear flag");
   if (n > 0) {
     const float* xyz = static_cast<const float*>(B.xyz);
     HIP_TRY(ptr::launch_finite_check(xyz, n, flag, st), "finite check");
@@ -355,10 +369,9 @@ pr_status pr_build_batches_spans(pr_ctx* ctx, pr_cloud* cloud, const uint32_t* s
         HIP_TRY(hipMemcpyAsync(B.nodes, nodes, sizeof(pr_lod_node) * nb, hipMemcpyHostToDevice, st), "nodes");
     }
   }
-  uint32_t h_flag = 0;
-  HIP_TRY(hipMemcpyAsync(&h_flag, flag, sizeof h_flag, hipMemcpyDeviceToHost, st), "read flag");
-  HIP_TRY(hipStreamSynchronize(st), "build");
-  if (h_flag) return fail(PR_ENONFINITE, "pr_build_batches_spans: a coordinate is NaN or Inf");
+  uint32_t seen[2];
+  if (pr_status s = read_flags(ctx, seen)) return s;
+  if (seen[0]) return fail(PR_ENONFINITE, "pr_build_batches_spans: a coordinate is NaN or Inf");
   cloud->nb = nb;
   cloud->batch_size = 0;
   cloud->morton = 0;
@@ -393,38 +406,42 @@ pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, in
   hipStream_t st = ctx->stream;
   const uint64_t nb = (n + batch_size - 1) / batch_size;
   cloud->built = 0;
-  uint32_t* flag = &ctx->dev->flags[0];
-  HIP_TRY(hipMemsetAsync(flag, 0, sizeof(uint32_t), st), "clear flag");
+  uint32_t* const flags = &ctx->dev->flags[0];  // [0] non-finite coordinate, [1] a run left unsorted
+  uint32_t seen[2] = {0, 0};
   if (n > 0) {
-    const float* xyz = static_cast<const float*>(B.xyz);
-    const uint32_t* rgba = static_cast<const uint32_t*>(B.rgba);
-    uint32_t* perm = static_cast<uint32_t*>(B.perm);
-    uint32_t* colors = static_cast<uint32_t*>(B.colors);
+    ptr::BuildArgs a;
+    a.xyz = static_cast<float*>(B.xyz);
+    a.rgba = static_cast<const uint32_t*>(B.rgba);
+    a.n = n;
+    a.S = batch_size;
+    a.colors = static_cast<uint32_t*>(B.colors);
+    a.perm = static_cast<uint32_t*>(B.perm);
+    a.batches = static_cast<ptr::BatchRec*>(B.batches);
+    a.low = static_cast<uint32_t*>(B.low);
+    a.med = static_cast<uint32_t*>(B.med);
+    a.high = static_cast<uint32_t*>(B.high);
+    a.nonfinite = flags;
     if (morton) {
       ptr::SortScratch sc;
-      uint8_t* base = static_cast<uint8_t*>(B.scratch) + ptr::small_scratch_bytes();
-      ptr::sort_scratch_layout(n, base, &sc);
-      HIP_TRY(ptr::launch_morton_codes(xyz, n, sc.aabb, sc.keys0, perm, flag, st), "morton codes");
-      HIP_TRY(ptr::radix_sort_pairs(sc, perm, n, st), "radix sort");
-      // sorted positions straight into the caller's xyz buffer (the gather reads copies of the inputs)
-      HIP_TRY(ptr::launch_gather(sc, xyz, rgba, perm, n, batch_size, morton == PR_ORDER_MORTON_SPREAD,
-                                 static_cast<float*>(B.xyz), colors, st),
-              "gather");
+      ptr::sort_scratch_layout(n, static_cast<uint8_t*>(B.scratch), &sc);
+      if (sc.end > ptr::small_scratch_bytes() + ptr::sort_scratch_bytes(n))
+        return fail(PR_EINVAL, "pr_build_batches: the sort areas exceed the scratch buffer");
+      const bool spread = morton == PR_ORDER_MORTON_SPREAD;
+      for (bool full : {false, true}) {
+        if (full) HIP_TRY(ptr::launch_restore(sc, n, a.xyz, st), "positions of the input order");
+        HIP_TRY(ptr::launch_morton_sort(sc, a.xyz, a.perm, n, full, flags, flags + 1, st), "Morton sort");
+        HIP_TRY(ptr::launch_build_sorted(a, sc, spread, st), "batches");
+        if (pr_status s = read_flags(ctx, seen)) return s;
+        // a run of points that the sort's leading bits leave equal, too long for the short way and out of
+        // order (a few points far from all others): again with every bit
+        if (seen[0] || !seen[1]) break;
+      }
     } else {
-      HIP_TRY(ptr::launch_finite_check(xyz, n, flag, st), "finite check");
-      HIP_TRY(ptr::launch_iota(perm, n, st), "iota");
-      HIP_TRY(hipMemcpyAsync(colors, rgba, 4 * n, hipMemcpyDeviceToDevice, st), "copy colours");
+      HIP_TRY(ptr::launch_build_input(a, st), "batches");
+      if (pr_status s = read_flags(ctx, seen)) return s;
     }
-    ptr::BatchRec* batches = static_cast<ptr::BatchRec*>(B.batches);
-    HIP_TRY(ptr::launch_batch_bbox(xyz, n, batch_size, nb, batches, st), "batch boxes");
-    HIP_TRY(ptr::launch_quantize(xyz, n, batch_size, batches, static_cast<uint32_t*>(B.low),
-                                 static_cast<uint32_t*>(B.med), static_cast<uint32_t*>(B.high), st),
-            "quantise");
   }
-  uint32_t h_flag = 0;
-  HIP_TRY(hipMemcpyAsync(&h_flag, flag, sizeof h_flag, hipMemcpyDeviceToHost, st), "read flag");
-  HIP_TRY(hipStreamSynchronize(st), "build");
-  if (h_flag) return fail(PR_ENONFINITE, "pr_build_batches: a coordinate is NaN or Inf");
+  if (seen[0]) return fail(PR_ENONFINITE, "pr_build_batches: a coordinate is NaN or Inf");
   cloud->nb = nb;
   cloud->batch_size = batch_size;
   cloud->morton = morton;
