@@ -1,6 +1,17 @@
 // High-quality shading pass (Sec. 3.6) for gfx950: the sums of the colours of
 // the points near each pixel's closest depth, and their average.
 //
+// What bounds it: the device's atomics where batches add straight into global
+// sums (25 G 64-byte lines/s), and the latency chain of a batch (record,
+// thresholds, words, flush) with two workgroups per CU.  At 5e8 points, one
+// 2016x2240 eye of 1.4e4 live batches: 495 us with both words of a pixel in
+// instructions of their own, a point's threshold read and addition before the
+// next point's, and sums and thresholds staged before the words were asked
+// for; 480 with one instruction per pixel in the flush; 385 with the same for
+// the untiled batches (6 % of the points); 370 as it stands.  Smaller
+// workgroups with smaller tiles (4 or 5 waves, 2032 pixels: 435 and 445 us)
+// and larger ones (10 or 16 waves: 525 and 490) are slower.
+//
 // Its own translation unit: the pass runs eight-wave workgroups (two per CU,
 // each with an 80 KiB LDS tile of thresholds and sums) over the point loops
 // of raster_core.h.
@@ -18,34 +29,47 @@ namespace {
 // flush each covered pixel with two global additions; the others read the
 // visibility buffer and add globally per point.  Integer sums: the result
 // does not depend on the order of the additions.
-// 4064 pixels: 16 KiB of thresholds + 64 KiB of sums (+ s_next), two workgroups in 160 KiB of LDS
-constexpr uint32_t HQS_TILE = 4064;
+
+// Row of entry e of a rectangle of tw columns, m = row_magic(tw): exact while
+// e * tw < 2^32.
+__device__ __forceinline__ uint32_t row_magic(uint32_t tw) { return 0xFFFFFFFFu / tw + 1u; }  // 0 for one column
+__device__ __forceinline__ uint32_t row_of(uint32_t e, uint32_t m) { return m ? __umulhi(e, m) : e; }
 
 // Thresholds fl32(closest depth * window) of a tw x th rectangle at (x0, y0)
-// into the LDS tile, and its sums zeroed.
-__device__ __forceinline__ void stage_band(const RenderArgs& a, float* thr, uint64_t* sums, uint32_t tid, uint32_t x0,
-                                           uint32_t y0, uint32_t tw, uint32_t th) {
-  const uint32_t n = tw * th;
-  for (uint32_t e = tid; e < n; e += THREADS) {
-    const uint32_t ly = e / tw, lx = e - ly * tw;
-    const uint64_t key = a.vb[(y0 + ly) * a.W + (x0 + lx)];
-    thr[e] = __uint_as_float((uint32_t)(key >> 32)) * a.window;
-    sums[2 * e] = 0;
-    sums[2 * e + 1] = 0;
+// into the LDS tile, four reads of a thread in flight.
+__device__ __forceinline__ void stage_band(const RenderArgs& a, float* thr, uint32_t tid, uint32_t x0, uint32_t y0,
+                                           uint32_t tw, uint32_t th) {
+  const uint32_t n = tw * th, m = row_magic(tw);
+  const uint32_t* const depth = reinterpret_cast<const uint32_t*>(a.vb + ((uint64_t)y0 * a.W + x0)) + 1;
+  for (uint32_t b = tid; b < n; b += 4 * THREADS) {
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t e = min(b + j * THREADS, n - 1u), ly = row_of(e, m);
+      d[j] = depth[2 * (uint64_t)(ly * a.W + (e - ly * tw))];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (b + j * THREADS < n) thr[b + j * THREADS] = __uint_as_float(d[j]) * a.window;
   }
 }
 
-// Every pixel of the rectangle with a point in its sums: two global additions.
-__device__ __forceinline__ void flush_band(const RenderArgs& a, const uint64_t* sums, uint32_t tid, uint32_t x0,
-                                           uint32_t y0, uint32_t tw, uint32_t th) {
-  const uint32_t n = tw * th;
-  for (uint32_t e = tid; e < n; e += THREADS) {
-    const uint64_t bn = sums[2 * e + 1];
+// Every pixel of the rectangle with a point in its sums: two global additions,
+// by neighbouring lanes; the sums are left zero for the next batch.  The
+// device's atomics cost by the 64-byte line of an instruction (25 G lines/s),
+// so the two words of a pixel go into one.
+__device__ __forceinline__ void flush_band(const RenderArgs& a, uint64_t* sums, uint32_t tid, uint32_t x0, uint32_t y0,
+                                           uint32_t tw, uint32_t th) {
+  const uint32_t n = tw * th, m = row_magic(tw), half = tid & 1u;
+  uint64_t* const base = a.accum + 2 * ((uint64_t)y0 * a.W + x0) + half;
+  for (uint32_t e = tid >> 1; e < n; e += THREADS / 2) {
+    const uint64_t bn = sums[HQS_TILE + e];
     if (bn >> 32) {
-      const uint32_t ly = e / tw, lx = e - ly * tw;
-      uint64_t* const g = a.accum + 2 * (uint64_t)((y0 + ly) * a.W + (x0 + lx));
-      __hip_atomic_fetch_add(g, sums[2 * e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(g + 1, bn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t v = half ? bn : sums[e];
+      sums[half * HQS_TILE + e] = 0;  // after both lanes' reads: they are lanes of one wave
+      const uint32_t ly = row_of(e, m);
+      __hip_atomic_fetch_add(base + 2 * (uint64_t)(ly * a.W + (e - ly * tw)), v, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -62,6 +86,7 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
   const uint32_t nlive = a.hdr->live_count + a.hdr->direct_count;
   const uint32_t shift = slice_shift(nlive, gridDim.x);
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+  for (uint32_t e = tid; e < 2 * HQS_TILE; e += THREADS) sums[e] = 0;
   const Streams st = {a.low, a.med, a.high, a.colors};
   __syncthreads();
   uint32_t p = uni(s_next);
@@ -111,9 +136,10 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
       for (uint32_t by = by0; by < by1; by += bh) {
         L.th = min(bh, by1 - by);
         L.cy = in_vgpr(uni(0x4B000000u + y0 + by));
-        stage_band(a, thr, sums, tid, x0, y0 + by, L.tw, L.th);
-        __syncthreads();
-        raster_by_class<10, true, true, true>(cls, L, st, sums, first, count, wave, lane, natom);
+        raster_by_class<10, true, true, true>(cls, L, st, sums, first, count, wave, lane, natom, [&] {
+          stage_band(a, thr, tid, x0, y0 + by, L.tw, L.th);
+          __syncthreads();
+        });
         __syncthreads();  // the band's sums are complete; s_next has been read
         if (by == by0 && tid == 0) s_next = grab;
         flush_band(a, sums, tid, x0, y0 + by, L.tw, L.th);
@@ -130,11 +156,14 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     L.cx = in_vgpr(uni(0x4B000000u + (tiled ? x0 : 0u)));
     L.cy = in_vgpr(uni(0x4B000000u + (tiled ? y0 : 0u)));
     if (tiled) {
-      stage_band(a, thr, sums, tid, x0, y0, L.tw, L.th);
-      __syncthreads();
-      if (k == 10) raster_by_class<10, true, true>(cls, L, st, sums, first, count, wave, lane, natom);
-      else if (k == 20) raster_by_class<20, true, true>(cls, L, st, sums, first, count, wave, lane, natom);
-      else raster_by_class<30, true, true>(cls, L, st, sums, first, count, wave, lane, natom);
+      // the thresholds are read while the wave's first words are on their way
+      const auto stage = [&] {
+        stage_band(a, thr, tid, x0, y0, L.tw, L.th);
+        __syncthreads();
+      };
+      if (k == 10) raster_by_class<10, true, true>(cls, L, st, sums, first, count, wave, lane, natom, stage);
+      else if (k == 20) raster_by_class<20, true, true>(cls, L, st, sums, first, count, wave, lane, natom, stage);
+      else raster_by_class<30, true, true>(cls, L, st, sums, first, count, wave, lane, natom, stage);
     } else {
       if (k == 10) raster_by_class<10, false, true>(cls, L, st, sums, first, count, wave, lane, natom);
       else if (k == 20) raster_by_class<20, false, true>(cls, L, st, sums, first, count, wave, lane, natom);
@@ -148,12 +177,11 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
   }
 }
 
-__global__ void __launch_bounds__(64) k_reset_queues(FrameHeader* hdr) {
-  if (threadIdx.x < RENDER_QUEUES) hdr->queue[threadIdx.x][0] = 0;
-}
-
-__global__ void __launch_bounds__(256) k_zero64(uint64_t* p, uint64_t n) {
+// Zeroes the sums and, in its first block, the work-queue counters that the
+// frame's render has used up.
+__global__ void __launch_bounds__(256) k_zero_sums(uint64_t* p, uint64_t n, FrameHeader* hdr) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  if (blockIdx.x == 0 && threadIdx.x < RENDER_QUEUES && hdr) hdr->queue[threadIdx.x][0] = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0;
 }
 
@@ -188,10 +216,9 @@ hipError_t launch_accumulate(const RenderArgs& a, hipStream_t s) {
   const uint64_t n = 2ull * a.W * a.H;
   uint64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_zero64, dim3((uint32_t)blocks), dim3(256), 0, s, a.accum, n);
-  if (a.nb == 0) return hipGetLastError();
   // the shading pass walks the render's live list with fresh work-queue counters
-  hipLaunchKernelGGL(k_reset_queues, dim3(1), dim3(64), 0, s, a.hdr);
+  hipLaunchKernelGGL(k_zero_sums, dim3((uint32_t)blocks), dim3(256), 0, s, a.accum, n, a.nb ? a.hdr : nullptr);
+  if (a.nb == 0) return hipGetLastError();
   const uint64_t items = (uint64_t)a.nb << MAX_SLICE_SHIFT;
   const uint32_t blocks_r = a.grid < items ? a.grid : (uint32_t)items;
   hipLaunchKernelGGL(k_accum, dim3(blocks_r), dim3(THREADS), 0, s, a);

@@ -126,6 +126,27 @@ __device__ __forceinline__ uint64_t sum_rg(uint32_t c) {
 }
 __device__ __forceinline__ uint64_t sum_bn(uint32_t c) { return (uint64_t)((c >> 16) & 255u) | (1ull << 32); }
 
+// LDS tile of the shading pass: 4064 pixels, 16 KiB of thresholds, 32 KiB of
+// red and green sums, then 32 KiB of blue sums and counts (+ s_next): two
+// workgroups in 160 KiB of LDS.  The two halves of a pixel's sums are apart so
+// that the additions of neighbouring pixels fall into neighbouring banks.
+constexpr uint32_t HQS_TILE = 4064;
+
+// One global addition per lane for the points of every second lane: the even
+// lane of a pair adds the red and green of the pair's even (CTRL: quad_perm
+// 0,0,2,2) or odd (1,1,3,3) point, the odd lane its blue and count.  Both words
+// of a pixel go out in one instruction, which costs the device's atomics one
+// line instead of two.
+template <int CTRL>
+__device__ __forceinline__ void add_pair(uint64_t* acc, bool in, uint32_t e, uint32_t c) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)(in ? e : ~0u), CTRL, 0xF, 0xF, true);
+  const uint32_t v = (uint32_t)__builtin_amdgcn_mov_dpp((int)c, CTRL, 0xF, 0xF, true);
+  const uint32_t half = threadIdx.x & 1u;
+  if (o != ~0u)
+    __hip_atomic_fetch_add(acc + 2 * (uint64_t)o + half, half ? sum_bn(v) : sum_rg(v), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Shading pass, four consecutive points of one lane: a drawn point joins its
 // pixel's sums iff hw <= fl32(closest depth * window).  Tiled batches add into
 // the LDS sums (tile) behind the LDS threshold tile; others read the closest
@@ -136,36 +157,109 @@ __device__ __forceinline__ void four_points_acc(const Loop& L, uint64_t* tile, c
   const uint32_t Mw[4] = {w.m.x, w.m.y, w.m.z, w.m.w};
   const uint32_t Hw[4] = {w.h.x, w.h.y, w.h.z, w.h.w};
   const uint32_t Cw[4] = {w.c.x, w.c.y, w.c.z, w.c.w};
+  // pixels and thresholds of the four points first, then their additions: one
+  // wait for the four reads
+  uint32_t e[4];
+  float hw[4], thr[4];
+  bool ok[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     float X, Y, Z;
     decode<K>(Lw[j], Mw[j], Hw[j], X, Y, Z);
     const Proj p = project(L, X, Y, Z);
-    bool ok = (uint32_t)j < nvalid;
-    if constexpr (CLS != CLS_INSIDE) ok = ok && visible(L, p);
+    hw[j] = p.hw;
+    ok[j] = (uint32_t)j < nvalid;
+    if constexpr (CLS != CLS_INSIDE) ok[j] = ok[j] && visible(L, p);
     uint32_t px, py;
     if constexpr (CLS == CLS_SLOW)
       pixel_exact(p, px, py);
     else
       pixel_fast(p, L.cx, L.cy, px, py);
     if constexpr (TILED) {
-      if constexpr (BAND) ok = ok && (py < L.th);  // rows of this band only
-      const uint32_t e = __umul24(py, L.tw) + px;
-      if (ok && p.hw <= L.thr[e]) {
-        __hip_atomic_fetch_add(&tile[2 * e], sum_rg(Cw[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&tile[2 * e + 1], sum_bn(Cw[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+      if constexpr (BAND) ok[j] = ok[j] && (py < L.th);  // rows of this band only
+      e[j] = __umul24(py, L.tw) + px;
     } else {
-      ok = ok && (px < L.W) && (py < L.H);
-      const uint32_t off = __umul24(py, L.W) + px;
-      if (ok) {
-        const uint64_t k = __hip_atomic_load(L.vb + off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (p.hw <= __uint_as_float((uint32_t)(k >> 32)) * L.window) {
-          __hip_atomic_fetch_add(L.acc + 2 * (uint64_t)off, sum_rg(Cw[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_fetch_add(L.acc + 2 * (uint64_t)off + 1, sum_bn(Cw[j]), __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-        }
+      ok[j] = ok[j] && (px < L.W) && (py < L.H);
+      e[j] = __umul24(py, L.W) + px;
+    }
+  }
+  if constexpr (TILED) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (CLS == CLS_INSIDE && !BAND) {
+        thr[j] = L.thr[e[j]];  // padding lanes decode to points of the box too
+      } else {
+        thr[j] = 0.f;
+        if (ok[j]) thr[j] = L.thr[e[j]];
       }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (ok[j] && hw[j] <= thr[j]) {
+        __hip_atomic_fetch_add(&tile[e[j]], sum_rg(Cw[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&tile[HQS_TILE + e[j]], sum_bn(Cw[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  } else {
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      d[j] = 0;
+      if (ok[j])
+        d[j] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(L.vb + e[j]) + 1, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = ok[j] && hw[j] <= __uint_as_float(d[j]) * L.window;
+      add_pair<0xA0>(L.acc, in, e[j], Cw[j]);  // even lanes' points
+      add_pair<0xF5>(L.acc, in, e[j], Cw[j]);  // odd lanes' points
+    }
+  }
+}
+
+// Four consecutive points of one lane straight into the visibility buffer, in
+// two steps: keys and early-depth reads, then the atomics of the keys that beat
+// them.
+struct Direct {
+  uint32_t off[4];
+  uint64_t key[4], old[4];  // old: 0 where nothing is to be written
+};
+template <int K, int CLS>
+__device__ __forceinline__ void direct_read(const Loop& L, const Words& w, uint32_t i0, uint32_t nvalid, Direct& q) {
+  const uint32_t Lw[4] = {w.l.x, w.l.y, w.l.z, w.l.w};
+  const uint32_t Mw[4] = {w.m.x, w.m.y, w.m.z, w.m.w};
+  const uint32_t Hw[4] = {w.h.x, w.h.y, w.h.z, w.h.w};
+  bool ok[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float X, Y, Z;
+    decode<K>(Lw[j], Mw[j], Hw[j], X, Y, Z);
+    const Proj p = project(L, X, Y, Z);
+    ok[j] = (uint32_t)j < nvalid;
+    if constexpr (CLS != CLS_INSIDE) ok[j] = ok[j] && visible(L, p);
+    uint32_t px, py;
+    if constexpr (CLS == CLS_SLOW)
+      pixel_exact(p, px, py);
+    else
+      pixel_fast(p, L.cx, L.cy, px, py);
+    // Never address outside the image, whatever the class proofs say.
+    ok[j] = ok[j] && (px < L.W) && (py < L.H);
+    q.off[j] = __umul24(py, L.W) + px;
+    q.key[j] = make_key(p.hw, i0 + j);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    q.old[j] = 0;
+    if (ok[j]) q.old[j] = __hip_atomic_load(L.vb + q.off[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  }
+}
+__device__ __forceinline__ void direct_write(const Loop& L, const Direct& q, uint32_t& natom) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (q.key[j] < q.old[j]) {
+      __hip_atomic_fetch_min(L.vb + q.off[j], q.key[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      natom++;
     }
   }
 }
@@ -231,39 +325,9 @@ __device__ __forceinline__ void four_points(const Loop& L, uint64_t* tile, const
         __hip_atomic_fetch_min(reinterpret_cast<uint64_t*>(tb + ad[j]), key[j], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
   } else {
-    uint32_t off[4];
-    uint64_t key[4], old[4];
-    bool ok[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float X, Y, Z;
-      decode<K>(Lw[j], Mw[j], Hw[j], X, Y, Z);
-      const Proj p = project(L, X, Y, Z);
-      ok[j] = (uint32_t)j < nvalid;
-      if constexpr (CLS != CLS_INSIDE) ok[j] = ok[j] && visible(L, p);
-      uint32_t px, py;
-      if constexpr (CLS == CLS_SLOW)
-        pixel_exact(p, px, py);
-      else
-        pixel_fast(p, L.cx, L.cy, px, py);
-      // Never address outside the image, whatever the class proofs say.
-      ok[j] = ok[j] && (px < L.W) && (py < L.H);
-      off[j] = __umul24(py, L.W) + px;
-      key[j] = make_key(p.hw, i0 + j);
-    }
-    // all early-depth reads first, then the atomics
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      old[j] = 0;
-      if (ok[j]) old[j] = __hip_atomic_load(L.vb + off[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (ok[j] && key[j] < old[j]) {
-        __hip_atomic_fetch_min(L.vb + off[j], key[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        natom++;
-      }
-    }
+    Direct q;
+    direct_read<K, CLS>(L, w, i0, nvalid, q);
+    direct_write(L, q, natom);
   }
 }
 
@@ -443,14 +507,19 @@ __device__ __forceinline__ Words load_group(const BatchStreams& b, uint32_t g, u
 // 16-byte load per word) and hands each lane's four points to
 // fn(words, index of the first, number valid).  The ragged tail goes to wave
 // ngrp mod WAVES, the next in that rotation (one of the waves with the fewest
-// groups).  PF groups are in flight per wave.
-template <int K, bool ACC, int PF, typename Fn>
+// groups).  PF groups are in flight per wave.  pre() runs once in every wave,
+// after the wave's first loads are issued.
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int K, bool ACC, int PF, typename Fn, typename Pre = Nothing>
 __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, uint32_t count, uint32_t wave,
-                                             uint32_t lane, Fn&& fn) {
+                                             uint32_t lane, Fn&& fn, Pre&& pre = Pre()) {
   const BatchStreams bs = batch_streams<K, ACC>(a, first);
   const uint32_t lane16 = lane * 16u;
   const uint32_t ngrp = count >> 8;
   const uint32_t nj = wave < ngrp ? (ngrp - wave + WAVES - 1) / WAVES : 0;  // this wave's groups
+  if (nj == 0) pre();
   if (nj > 0) {
     // PF register sets rotate through the wave's groups; each is
     // reloaded in place right after use, so every load is issued PF
@@ -473,6 +542,7 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
       // younger loads on every path
       __builtin_amdgcn_sched_barrier(0);
     }
+    pre();
     uint32_t left = nj;
     for (; left > PF; left -= PF) {
 #pragma unroll
@@ -511,27 +581,34 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
 }
 
 // The points of one batch into one view (tile or visibility buffer).
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false>
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
-                                             uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom) {
+                                             uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
+                                             Pre&& pre = Pre()) {
   // The rare SLOW class (binary64 floor) keeps one group in flight and the
   // rare 20- and 30-bit batches (two and three words per point) at most
   // three: deeper prefetch there would set the register count of the whole
   // kernel, which the 10-bit loops (almost every point) then pay for.
   constexpr int PF = CLS == CLS_SLOW ? 1 : (K == 10 ? PREFETCH : (PREFETCH < 3 ? PREFETCH : 3));
-  stream_chunk<K, ACC, PF>(a, first, count, wave, lane, [&](const Words& w, uint32_t i0, uint32_t nv) {
-    four_points<K, CLS, TILED, ACC, BAND>(L, tile, w, i0, nv, natom);
-  });
+  stream_chunk<K, ACC, PF>(
+      a, first, count, wave, lane,
+      [&](const Words& w, uint32_t i0, uint32_t nv) {
+        four_points<K, CLS, TILED, ACC, BAND>(L, tile, w, i0, nv, natom);
+      },
+      pre);
 }
 
 // A batch, in chunks of at most CHUNK_POINTS points (one chunk for every
-// batch of a regular build).
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false>
+// batch of a regular build).  pre() as in stream_chunk, once unless count is 0.
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_points(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
-                                              uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom) {
+                                              uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
+                                              Pre&& pre = Pre()) {
   for (uint32_t c0 = 0; c0 < count; c0 += CHUNK_POINTS) {
     const uint32_t n = count - c0 < CHUNK_POINTS ? count - c0 : CHUNK_POINTS;
-    raster_chunk<K, CLS, TILED, ACC, BAND>(L, a, tile, first + c0, n, wave, lane, natom);
+    raster_chunk<K, CLS, TILED, ACC, BAND>(L, a, tile, first + c0, n, wave, lane, natom, [&] {
+      if (c0 == 0) pre();
+    });
   }
 }
 
@@ -547,14 +624,14 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 
 
 // ------------------------------------------------------------------ render
-template <int K, bool TILED, bool ACC = false, bool BAND = false>
+template <int K, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_by_class(int cls, const Loop& L, const Streams& a, uint64_t* tile,
                                                 uint32_t first, uint32_t count, uint32_t wave, uint32_t lane,
-                                                uint32_t& natom) {
+                                                uint32_t& natom, Pre&& pre = Pre()) {
   if (cls == CLS_INSIDE)
-    raster_points<K, CLS_INSIDE, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom);
+    raster_points<K, CLS_INSIDE, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
   else if (cls == CLS_PARTIAL)
-    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom);
+    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
   else if constexpr (!TILED)
     raster_points<K, CLS_SLOW, false, ACC>(L, a, tile, first, count, wave, lane, natom);
 }

@@ -72,3 +72,30 @@ def test_few_batches(ctx, n, S):
         want = oracle.accumulate(B, c.view, c.proj, c.width, c.height, ref, 1.01)
         assert np.array_equal(acc.cpu().numpy().view(np.uint64)[:2 * px], want)
         assert np.array_equal(fb.cpu().numpy().view(np.uint32), oracle.resolve_hqs(want, 7))
+
+
+@pytest.mark.parametrize("S", [1280, 2836, 4100])
+@pytest.mark.parametrize("precision", [10, 20, 30])
+def test_untiled_groups(ctx, S, precision):
+    """Batches that span the image (points in no order), too many to be sliced: a wave's groups of 256 points in pairs,
+    odd numbers of groups and ragged tails, at each precision, straight into the visibility buffer and the sums."""
+    import torch
+    import paper_2204_01287_amd as pr
+
+    xyz, rgba = synth.primitives(5, 1100 * S)
+    o = np.random.default_rng(S).permutation(len(xyz))
+    xyz, rgba = np.ascontiguousarray(xyz[o]), np.ascontiguousarray(rgba[o])
+    say(f"untiled groups: S={S} precision={precision}")
+    dc, B = gpu_build(ctx, xyz, rgba, S, 0), oracle.build_cloud(xyz, rgba, S, morton=0)
+    c = synth.camera((50.0, -90.0, 80.0), (50, 50, 50), (0, 0, 1), 60.0, 1023, 701, 0.5, 5000.0)
+    px = c.width * c.height
+    vb = torch.empty(px, dtype=torch.int64, device="cuda")
+    acc = torch.empty(2 * px + px % 2, dtype=torch.int64, device="cuda")
+    fb = torch.empty(px, dtype=torch.int32, device="cuda")
+    pr.pr_render_hqs(ctx.handle, dc.handle, c.view, c.proj, c.width, c.height, pr.RenderOpts.make(precision=precision),
+                     1.01, vb, acc, 7, fb)
+    pr.pr_sync(ctx.handle)
+    ref, _ = oracle.render(B, c.view, c.proj, c.width, c.height, oracle.opts(precision=precision))
+    assert_vb_equal(vb.cpu().numpy().view(np.uint64), ref, c.width)
+    want = oracle.accumulate(B, c.view, c.proj, c.width, c.height, ref, 1.01, oracle.opts(precision=precision))
+    assert np.array_equal(acc.cpu().numpy().view(np.uint64)[:2 * px], want)
