@@ -580,8 +580,66 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
   }
 }
 
+// The groups of a chunk in pairs, for the untiled path: both groups' early-depth
+// reads are in flight before the first atomic, so a wave waits for half as many
+// round trips (a full batch's ten groups: five; 352 -> 346 us a frame at 1e9
+// points and 2016x2240, 142 -> 138 at 1e8 and 1920x1080; an odd last group is
+// worked alone: projecting it as a pair's empty half took the gain back).  Not in the multi-view
+// kernel: no gain there (64 views of 5e8 points: 5.25 ms with it, 5.20 without).  Same distribution of
+// groups and tail as stream_chunk.
+template <int K, int CLS>
+__device__ __forceinline__ void direct_chunk(const Loop& L, const Streams& a, uint32_t first, uint32_t count,
+                                             uint32_t wave, uint32_t lane, uint32_t& natom) {
+  const BatchStreams bs = batch_streams<K, false>(a, first);
+  const uint32_t lane16 = lane * 16u;
+  const uint32_t ngrp = count >> 8;
+  const uint32_t nj = wave < ngrp ? (ngrp - wave + WAVES - 1) / WAVES : 0;
+  constexpr int PF = K == 10 ? 4 : 2;
+  if (nj > 0) {
+    const uint32_t glast = wave + (nj - 1) * WAVES;
+    Words R[PF];
+    uint32_t gi[PF];
+#pragma unroll
+    for (int d = 0; d < PF; ++d) {
+      gi[d] = wave + d * WAVES;
+      R[d] = load_group<K, false>(bs, min(gi[d], glast), lane16);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (uint32_t left = nj;; left -= PF) {
+#pragma unroll
+      for (int d = 0; d < PF; d += 2) {
+        if ((uint32_t)d < left) {
+          Direct q0, q1;
+          direct_read<K, CLS>(L, R[d], first + gi[d] * 256 + lane * 4, 4u, q0);
+          if ((uint32_t)d + 1 < left) {
+            direct_read<K, CLS>(L, R[d + 1], first + gi[d + 1] * 256 + lane * 4, 4u, q1);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q1.key[j] = q1.old[j] = 0;
+          }
+          gi[d] += PF * WAVES;
+          gi[d + 1] += PF * WAVES;
+          if (left > PF) {
+            R[d] = load_group<K, false>(bs, min(gi[d], glast), lane16);
+            R[d + 1] = load_group<K, false>(bs, min(gi[d + 1], glast), lane16);
+          }
+          direct_write(L, q0, natom);
+          direct_write(L, q1, natom);
+        }
+      }
+      if (left <= PF) break;
+    }
+  }
+  const uint32_t rem = count & 255u;
+  if (rem && wave == ngrp % WAVES)  // the ragged tail alone
+    stream_chunk<K, false, 1>(a, first + ngrp * 256u, rem, 0, lane, [&](const Words& w, uint32_t i0, uint32_t nv) {
+      four_points<K, CLS, false>(L, nullptr, w, i0, nv, natom);
+    });
+}
+
 // The points of one batch into one view (tile or visibility buffer).
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
+// PAIRS: the untiled loops of the single-view kernel (direct_chunk).
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
                                              uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
                                              Pre&& pre = Pre()) {
@@ -589,6 +647,10 @@ __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, ui
   // rare 20- and 30-bit batches (two and three words per point) at most
   // three: deeper prefetch there would set the register count of the whole
   // kernel, which the 10-bit loops (almost every point) then pay for.
+  if constexpr (PAIRS && !TILED && !ACC && CLS != CLS_SLOW) {
+    direct_chunk<K, CLS>(L, a, first, count, wave, lane, natom);
+    return;
+  }
   constexpr int PF = CLS == CLS_SLOW ? 1 : (K == 10 ? PREFETCH : (PREFETCH < 3 ? PREFETCH : 3));
   stream_chunk<K, ACC, PF>(
       a, first, count, wave, lane,
@@ -600,13 +662,13 @@ __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, ui
 
 // A batch, in chunks of at most CHUNK_POINTS points (one chunk for every
 // batch of a regular build).  pre() as in stream_chunk, once unless count is 0.
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_points(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
                                               uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
                                               Pre&& pre = Pre()) {
   for (uint32_t c0 = 0; c0 < count; c0 += CHUNK_POINTS) {
     const uint32_t n = count - c0 < CHUNK_POINTS ? count - c0 : CHUNK_POINTS;
-    raster_chunk<K, CLS, TILED, ACC, BAND>(L, a, tile, first + c0, n, wave, lane, natom, [&] {
+    raster_chunk<K, CLS, TILED, ACC, BAND, PAIRS>(L, a, tile, first + c0, n, wave, lane, natom, [&] {
       if (c0 == 0) pre();
     });
   }
@@ -624,14 +686,14 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 
 
 // ------------------------------------------------------------------ render
-template <int K, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
+template <int K, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_by_class(int cls, const Loop& L, const Streams& a, uint64_t* tile,
                                                 uint32_t first, uint32_t count, uint32_t wave, uint32_t lane,
                                                 uint32_t& natom, Pre&& pre = Pre()) {
   if (cls == CLS_INSIDE)
-    raster_points<K, CLS_INSIDE, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
+    raster_points<K, CLS_INSIDE, TILED, ACC, BAND, PAIRS>(L, a, tile, first, count, wave, lane, natom, pre);
   else if (cls == CLS_PARTIAL)
-    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
+    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND, PAIRS>(L, a, tile, first, count, wave, lane, natom, pre);
   else if constexpr (!TILED)
     raster_points<K, CLS_SLOW, false, ACC>(L, a, tile, first, count, wave, lane, natom);
 }
@@ -727,6 +789,7 @@ __device__ __forceinline__ Span banded_part(Span b, uint32_t th, uint32_t bh, ui
 // per band.  publish: thread 0 stores next into s_next after the first
 // barrier (the workgroup reads it after the last one).  slice, shift: the part
 // of the batch to render (above; shift 0: all of it).
+template <bool PAIRS>
 __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, uint32_t H, uint64_t* vb,
                                              const Streams& st, uint64_t* tile, uint32_t tid, uint32_t wave,
                                              uint32_t lane, bool publish, uint32_t next, uint32_t* s_next,
@@ -785,9 +848,9 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
     else if (k == 20) raster_by_class<20, true>(cls, L, st, tile, first, count, wave, lane, natom);
     else raster_by_class<30, true>(cls, L, st, tile, first, count, wave, lane, natom);
   } else {
-    if (k == 10) raster_by_class<10, false>(cls, L, st, tile, first, count, wave, lane, natom);
-    else if (k == 20) raster_by_class<20, false>(cls, L, st, tile, first, count, wave, lane, natom);
-    else raster_by_class<30, false>(cls, L, st, tile, first, count, wave, lane, natom);
+    if (k == 10) raster_by_class<10, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
+    else if (k == 20) raster_by_class<20, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
+    else raster_by_class<30, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
   }
   __syncthreads();  // the batch's points are all in the tile; s_next has been read
   if (publish && tid == 0) *s_next = next;
@@ -958,7 +1021,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
     // Take the next position now; the atomic's latency hides behind this batch.
     uint32_t grab = 0;
     if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift, natom);
+    render_batch<true>(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift, natom);
     p = uni(s_next);
     i = live_slot(p >> shift, nt, nd, rate, a.nb);
   }
@@ -1009,7 +1072,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
         }
       }
       const ViewOut& vo = a.v[v];
-      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift, natom);
+      render_batch<false>(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift, natom);
       publish = false;
     }
     p = uni(s_next);
