@@ -23,7 +23,7 @@ static_assert(sizeof(LodNode) == 48, "LOD node record is 48 bytes");
 // Device-side context block (one per pr_ctx), 4 KiB.
 struct DevBlock {
   uint64_t stats[16];     // batches, culled, points, lvl_b[3], lvl_p[3], atomics, words bytes
-  uint32_t flags[16];     // [0] non-finite coordinate seen
+  uint32_t flags[16];     // [0] non-finite coordinate seen, [1] Morton codes left out of order
   uint64_t sink;          // streaming read probe
 };
 enum { ST_BATCHES = 0, ST_CULLED, ST_POINTS, ST_LB0, ST_LB1, ST_LB2, ST_LP0, ST_LP1, ST_LP2, ST_ATOMICS, ST_WORDS };

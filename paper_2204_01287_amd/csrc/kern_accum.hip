@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
   // batch order (Morton order for sorted clouds): the sums' lines of neighbouring
   // batches stay in the caches; measured faster than the render's order here
   const uint32_t nlive = a.hdr->live_count + a.hdr->direct_count;
-  const uint32_t shift = slice_shift(nlive, gridDim.x);
+  const uint32_t shift = slice_shift(nlive, a.hdr->direct_count, gridDim.x);
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   for (uint32_t e = tid; e < 2 * HQS_TILE; e += THREADS) sums[e] = 0;
   const Streams st = {a.low, a.med, a.high, a.colors};

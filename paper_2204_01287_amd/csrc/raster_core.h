@@ -741,13 +741,17 @@ __device__ __forceinline__ void flush_tile(uint64_t* tile, uint32_t tid, uint64_
 // deals out its bands first, so that a part streams its points for one band
 // only.  Slices without a part do nothing.  Frames of as many batches as
 // workgroups or more are not cut: slices of their last batches alone gained
-// nothing.  Pass times, before and after: 2e4 points at 641x479 51 -> 18 us,
+// nothing.  Nor are frames of many untiled batches: an eighth as many as there are
+// workgroups keep the device's atomics busy by themselves, and more waves at
+// once only read the buffer earlier and write more (205 untiled batches of 2e6
+// points at 2382x1923: kernel 66 us uncut, 72 in 16 slices, 70 in 2; 98 batches
+// of 1e6 at 1280x720: 45 uncut, 39 in 16).  Pass times, before and after: 2e4 points at 641x479 51 -> 18 us,
 // 2e5 at 2116x1607 37 -> 21, 1e6 at 1280x720 60 -> 50, shading of 1.2e5 points
 // at 1206x751 150 -> 39.
-__device__ __forceinline__ uint32_t slice_shift(uint32_t items, uint32_t grid) {
+__device__ __forceinline__ uint32_t slice_shift(uint32_t items, uint32_t untiled, uint32_t grid) {
   uint32_t shift = 0;
   while (shift < MAX_SLICE_SHIFT && (items << shift) < 2u * grid) ++shift;
-  return items < grid ? shift : 0u;
+  return items < grid && untiled < grid * WAVES / 32u ? shift : 0u;  // grids of four-wave workgroups: an eighth
 }
 struct Span {
   uint32_t first, count;
@@ -1011,7 +1015,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  const uint32_t shift = slice_shift(nt + nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
@@ -1041,7 +1045,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  const uint32_t shift = slice_shift(nt + nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
