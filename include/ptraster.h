@@ -140,7 +140,8 @@ const char* pr_last_error(void);
 
 /* Create a context on HIP device `device`, enqueuing on `hip_stream` (a
  * hipStream_t; NULL = the null stream).  Allocates 4 KiB of device memory for
- * frame constants and counters.  PR_EDEVICE if no GPU is usable. */
+ * frame constants and counters and 256 bytes of pinned host memory for the
+ * build's flags.  PR_EDEVICE if no GPU is usable. */
 pr_status pr_create(int device, void* hip_stream, pr_ctx** out);
 void pr_destroy(pr_ctx* ctx);
 
@@ -185,7 +186,9 @@ enum {
  * shortens the queues on them (the render and two-view passes are faster;
  * pr_resolve's colour gather is a little less coherent).  perm and colors
  * follow the stored order.  Synchronises the
- * stream once.  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for
+ * stream once (twice where the leading bits of the codes leave too many
+ * points together, a few points far from all others: these are sorted again
+ * over every bit).  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for
  * an unknown order. */
 pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, int morton);
 
@@ -353,7 +356,8 @@ typedef struct {
   uint32_t wg_per_cu; /* persistent workgroups per CU, at most what fits; 0 = all that fit [0] */
   uint32_t max_bands; /* a 10-bit batch larger than the tile bound, at most one tile wide and
                          at most max_bands tiles large, renders in bands of rows through
-                         the LDS tile (1 = never, at most 64); 0 = 4 [0]                    */
+                         the LDS tile (1 = never, at most 64); 0 = 4, and up to 16 in frames
+                         of too few batches to occupy every workgroup [0]                  */
 } pr_tuning;
 
 /* The compiled shapes in index order (shape 0 is the default): writes
