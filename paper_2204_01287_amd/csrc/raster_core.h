@@ -753,6 +753,13 @@ __device__ __forceinline__ uint32_t slice_shift(uint32_t items, uint32_t untiled
   while (shift < MAX_SLICE_SHIFT && (items << shift) < 2u * grid) ++shift;
   return items < grid && untiled < grid * WAVES / 32u ? shift : 0u;  // grids of four-wave workgroups: an eighth
 }
+// Uncut frames of fewer batches than workgroups: one workgroup per batch (and one
+// per queue at least) stays, in launch order, so that the batches lie on as many
+// CUs as there are; left to all, the first workgroups of a CU took several.
+__device__ __forceinline__ bool surplus(uint32_t items, uint32_t shift) {
+  return shift == 0 && blockIdx.x >= items && blockIdx.x >= RENDER_QUEUES && items < gridDim.x &&
+         blockIdx.x >= (items + RENDER_QUEUES - 1) / RENDER_QUEUES * RENDER_QUEUES;
+}
 struct Span {
   uint32_t first, count;
 };
@@ -1016,6 +1023,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
   const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  if (surplus(nt + nd, shift)) return;
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
@@ -1046,6 +1054,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
   const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
+  if (surplus(nt + nd, shift)) return;
   if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
