@@ -38,8 +38,9 @@ const ptr::RasterShape& shape_at(uint32_t i) { return *kShapeOf[i](); }
 struct pr_ctx {
   int device;
   hipStream_t stream;
-  ptr::DevBlock* dev;  // counters and flags (device memory); the flags are 0 between builds
+  ptr::DevBlock* dev;  // counters and flags (device memory)
   uint32_t* seen;      // a build's flags on the host (pinned)
+  bool flags_dirty;    // a build may have left flags raised: cleared before the next one
   uint32_t cus;                     // compute units of the device
   uint32_t per_cu[kNumShapes][2];   // workgroups per CU that fit at once: single-view, multi-view kernel
   uint32_t accum_grid;              // persistent workgroups of the shading pass
@@ -200,6 +201,14 @@ hipError_t timed_launch(pr_ctx* ctx, Launch&& launch) {
   return hipEventRecord(ev[1], ctx->stream);
 }
 
+// Before the first launch of a build that raises flags.  They are 0 after every build that read_flags has seen to
+// its end; one that failed earlier may have raised some, so they are cleared here then.
+pr_status take_flags(pr_ctx* ctx) {
+  if (ctx->flags_dirty) HIP_TRY(hipMemsetAsync(&ctx->dev->flags[0], 0, sizeof ctx->dev->flags, ctx->stream), "clear flags");
+  ctx->flags_dirty = true;
+  return PR_OK;
+}
+
 // The build flags once the stream has reached this point, into seen; a raised one is cleared for the next build.
 pr_status read_flags(pr_ctx* ctx, uint32_t (&seen)[2]) {
   uint32_t* const flags = &ctx->dev->flags[0];
@@ -207,6 +216,7 @@ pr_status read_flags(pr_ctx* ctx, uint32_t (&seen)[2]) {
   HIP_TRY(hipStreamSynchronize(ctx->stream), "build");
   std::memcpy(seen, ctx->seen, sizeof seen);
   if (seen[0] || seen[1]) HIP_TRY(hipMemsetAsync(flags, 0, sizeof seen, ctx->stream), "clear flags");
+  ctx->flags_dirty = false;
   return PR_OK;
 }
 
@@ -234,6 +244,7 @@ pr_status pr_create(int device, void* hip_stream, pr_ctx** out) {
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->dev = nullptr;
   c->seen = nullptr;
+  c->flags_dirty = false;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) cus = 1;
   c->cus = (uint32_t)cus;
@@ -353,6 +364,7 @@ pr_status pr_build_batches_spans(pr_ctx* ctx, pr_cloud* cloud, const uint32_t* s
     recs[b].count = spans[2 * b + 1];
   }
   uint32_t* flag = &ctx->dev->flags[0];
+  if (pr_status s = take_flags(ctx)) return s;
   if (n > 0) {
     const float* xyz = static_cast<const float*>(B.xyz);
     HIP_TRY(ptr::launch_finite_check(xyz, n, flag, st), "finite check");
@@ -409,6 +421,7 @@ pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, in
   uint32_t* const flags = &ctx->dev->flags[0];  // [0] non-finite coordinate, [1] a run left unsorted
   uint32_t seen[2] = {0, 0};
   if (n > 0) {
+    if (pr_status s = take_flags(ctx)) return s;
     ptr::BuildArgs a;
     a.xyz = static_cast<float*>(B.xyz);
     a.rgba = static_cast<const uint32_t*>(B.rgba);
