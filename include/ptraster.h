@@ -187,8 +187,8 @@ enum {
  * pr_resolve's colour gather is a little less coherent).  perm and colors
  * follow the stored order.  Synchronises the
  * stream once (twice where the leading bits of the codes leave too many
- * points together, a few points far from all others: these are sorted again
- * over every bit).  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for
+ * points together, as in a dense spot or beside a few points far from all
+ * others: the sort then goes on over every bit).  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for
  * an unknown order. */
 pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, int morton);
 

@@ -219,12 +219,15 @@ void sort_scratch_layout(uint64_t n, uint8_t* scratch, SortScratch* out);
 hipError_t launch_finite_check(const float* xyz, uint64_t n, uint32_t* flag, hipStream_t s);
 hipError_t launch_iota(uint32_t* p, uint64_t n, hipStream_t s);
 // The stable Morton order of the points: sc.vals1[rank] = index (perm: working
-// memory).  nonfinite: set if a coordinate is NaN or Inf.  full: every bit of
-// the codes by radix passes; else the leading bits, and the runs they leave
-// equal in LDS, with unsorted set if a run was too long for that (the order is
-// then wrong and the caller sorts again in full).
-hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, bool full,
-                              uint32_t* nonfinite, uint32_t* unsorted, hipStream_t s);
+// memory).  nonfinite: set if a coordinate is NaN or Inf.  The leading bits of
+// the codes by radix passes, then the runs they leave equal in LDS; unsorted is
+// set if a run was too long for that, and the order is then to be finished by
+// launch_morton_resort.
+hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, uint32_t* nonfinite,
+                              uint32_t* unsorted, hipStream_t s);
+// The order by every bit of the codes, from the keys and the order in perm that
+// launch_morton_sort left (both stable, so points of equal codes stay in order).
+hipError_t launch_morton_resort(const SortScratch& sc, uint32_t* perm, uint64_t n, hipStream_t s);
 struct BuildArgs {
   float* xyz;
   const uint32_t* rgba;
@@ -233,24 +236,20 @@ struct BuildArgs {
   uint32_t *colors, *perm;
   BatchRec* batches;
   uint32_t *low, *med, *high;
-  uint32_t* nonfinite;
+  uint32_t *nonfinite, *unsorted;
 };
 // Batches of a.S points in input order, with the finite check: colours, perm, boxes, words.
 hipError_t launch_build_input(const BuildArgs& a, hipStream_t s);
 // The same in the order of sc.vals1 (positions too, in place), through 16-byte
 // records in the key buffers.  spread: every batch (the last one shorter) in the
 // spread order (position r <- Morton rank (r * m) mod c, m = spread_step(c)).
+// Changes nothing if *a.unsorted is set.
 hipError_t launch_build_sorted(const BuildArgs& a, const SortScratch& sc, bool spread, hipStream_t s);
-// The input positions again, from the records of launch_build_sorted.
-hipError_t launch_restore(const SortScratch& sc, uint64_t n, float* xyz, hipStream_t s);
 // the first integer >= floor(c / 4) + 1 coprime with c
 uint64_t spread_step(uint64_t c);
-hipError_t launch_batch_bbox(const float* xyz, uint64_t n, uint32_t S, uint64_t nb, BatchRec* out, hipStream_t s);
 // variable-size batches: recs[b].first / .count are set, the boxes are filled in
 hipError_t launch_batch_bbox_spans(const float* xyz, uint64_t nb, BatchRec* recs, hipStream_t s);
 hipError_t launch_quantize_spans(const float* xyz, uint64_t nb, const BatchRec* recs, uint32_t* low, uint32_t* med,
                                  uint32_t* high, hipStream_t s);
-hipError_t launch_quantize(const float* xyz, uint64_t n, uint32_t S, const BatchRec* batches, uint32_t* low,
-                           uint32_t* med, uint32_t* high, hipStream_t s);
 
 }  // namespace ptr

@@ -4,6 +4,11 @@
 //  sort (radix passes over the code's leading bits, then the runs that these
 //  leave equal, in LDS) -> records of position and colour -> per batch: gather,
 //  box, Eq. 1 words (one kernel).  Input order: the last kernel alone.
+//  Uneven clouds, where a run is too long for LDS: the sort goes on over every
+//  bit, and the kernels after it, which did nothing, run then.  A build with one
+//  point 1,000 extents away, by one sort of every bit in 8-bit passes as it was at
+//  first, by a build that was made and thrown away, and now: 2e5 points 460, 890,
+//  421 us; 2e7 4.30, 8.20, 3.14 ms; 5e8 74-79, 195-200, 72.5 ms.
 //
 // Boxes order binary32 values by IEEE totalOrder (-0 below +0) through the
 // monotone integer map okey(), so a box depends only on the point set, not on
@@ -78,8 +83,11 @@ __device__ __forceinline__ Box block_box(Box b, Box* red) {
   return b;
 }
 __device__ __forceinline__ bool not_finite(float f) { return (__float_as_uint(f) & 0x7F800000u) == 0x7F800000u; }
+// A look first: where every wave has cause, the atomics of millions of waves on one word would queue.
 __device__ __forceinline__ void raise(uint32_t* flag, bool bad) {
-  if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+  if (__ballot(bad) != 0 && (threadIdx.x & 63) == 0 &&
+      __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+    atomicOr(flag, 1u);
 }
 
 // The cloud box, and the finite check on the same loads (flag: set if a
@@ -305,6 +313,54 @@ __global__ void __launch_bounds__(256) k_scan_apply(uint32_t* __restrict__ x, ui
   }
 }
 
+// The same scan of up to SCAN_SMALL values (8,192-point tiles of about a million points) by one workgroup in one
+// launch, all loads in flight together.  SMALL_FIGURES
+constexpr int SS_WAVES = 16, SS_THREADS = 64 * SS_WAVES, SS_ITEMS = 16;  // items of four values per thread
+constexpr uint64_t SCAN_SMALL = 4ull * SS_ITEMS * SS_THREADS;
+__global__ void __launch_bounds__(SS_THREADS) k_scan_small(uint32_t* __restrict__ x, uint64_t m) {
+  __shared__ uint32_t sums[SS_ITEMS * SS_WAVES];
+  static_assert(SS_ITEMS * SS_WAVES == 256, "four sums per lane of the first wave");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t m4 = (uint32_t)(m / 4);  // m is a multiple of the digits of a pass
+  uint4* const x4 = reinterpret_cast<uint4*>(x);
+  uint4 v[SS_ITEMS];
+  uint32_t ex[SS_ITEMS];
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    const uint32_t i = j * SS_THREADS + threadIdx.x;
+    v[j] = i < m4 ? x4[i] : make_uint4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    const uint32_t own = v[j].x + v[j].y + v[j].z + v[j].w;
+    uint32_t inc = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    ex[j] = inc - own;
+    if (lane == 63) sums[j * SS_WAVES + wave] = inc;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const uint4 s = reinterpret_cast<uint4*>(sums)[lane];
+    const uint32_t own = s.x + s.y + s.z + s.w;
+    uint32_t inc = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    const uint32_t e = inc - own;
+    reinterpret_cast<uint4*>(sums)[lane] = make_uint4(e, e + s.x, e + s.x + s.y, e + s.x + s.y + s.z);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < SS_ITEMS; ++j) {
+    const uint32_t i = j * SS_THREADS + threadIdx.x, e = ex[j] + sums[j * SS_WAVES + wave];
+    if (i < m4) x4[i] = make_uint4(e, e + v[j].x, e + v[j].x + v[j].y, e + v[j].x + v[j].y + v[j].z);
+  }
+}
+
 // Scatter of one pass.  Each wave ranks its 1,024 consecutive elements alone,
 // against digit counters of its own (ballots give the rank among equal digits
 // of a 64-element row, the counter carries it over the rows): no barrier until
@@ -406,14 +462,40 @@ __global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(
 }
 
 // Orders the runs of elements whose keys agree from bit shift up, by the whole
-// key, stably, and writes the values alone (the keys end here).  An element moves
-// left by the number of earlier ones of its run with a larger key and right by
-// the number of later ones with a smaller key: a walk over its run in LDS, cheap
-// for the short runs that sort_passes leaves.  Runs of more than RUN_MAX + 1
-// elements are left as they are; flag is set if one of them is out of order
-// (one of equal keys is not, however long).
+// key, stably, and writes the values alone (the keys stay as they are).  An
+// element moves left by the number of earlier ones of its run with a larger key
+// and right by the number of later ones with a smaller key.  Runs of more than
+// RUN_MAX + 1 elements are left as they are; flag is set if one of them is out
+// of order (one of equal keys is not, however long).
+//
+// Bound by its memory traffic where runs are short: 16 bytes an element at 4.8
+// TB/s (5e8 points of an even surface: 1.66 ms; 1.75 when every element walked
+// to the ends of its run).  How far a run reaches is found first, by doubling and
+// halving steps, so that no element of a long run walks it.  Whole builds, with
+// the walk and now: 5e8 points with a third of them equal 77 -> 42 ms, with the
+// box 8 times wider than the points (about a hundred a run) 59 -> 47.
 constexpr int FIX_THREADS = 256, FIX_ITEMS = 8, RUN_MAX = 256;
 constexpr int FIX_TILE = FIX_THREADS * FIX_ITEMS;
+
+// Elements of the run of mine = k[at] on one side (DIR -1: before it, 1: after it), RUN_MAX + 1 at most.  The keys are
+// in the order of their leading bits, so a run has no gaps.
+template <int DIR>
+__device__ __forceinline__ int run_side(const uint64_t* k, int at, uint64_t mine, int shift) {
+  const auto same = [&](int d) { return ((k[at + DIR * d] ^ mine) >> shift) == 0; };
+  int in = 0, out = 1;
+  while (out <= RUN_MAX && same(out)) {
+    in = out;
+    out *= 2;
+  }
+  out = min(out, RUN_MAX + 2);
+  while (out - in > 1) {
+    const int mid = (in + out) / 2;
+    if (same(mid)) in = mid;
+    else out = mid;
+  }
+  return in;
+}
+
 __global__ void __launch_bounds__(FIX_THREADS) k_fix_runs(const uint64_t* __restrict__ keys,
                                                           const uint32_t* __restrict__ vin, uint64_t n, int shift,
                                                           uint32_t* __restrict__ vout, uint32_t* __restrict__ flag) {
@@ -443,20 +525,15 @@ __global__ void __launch_bounds__(FIX_THREADS) k_fix_runs(const uint64_t* __rest
     if (i >= (int64_t)n) break;
     const int at = (int)(i - lo);
     const uint64_t mine = k[at];
-    int left = 0, right = 0, move = 0;
-    while (left <= RUN_MAX && ((k[at - left - 1] ^ mine) >> shift) == 0) {
-      ++left;
-      move -= k[at - left] > mine ? 1 : 0;
-      if (left > RUN_MAX) break;
-    }
-    while (right <= RUN_MAX && ((k[at + right + 1] ^ mine) >> shift) == 0) {
-      ++right;
-      move += k[at + right] < mine ? 1 : 0;
-      if (right > RUN_MAX) break;
-    }
+    const int left = run_side<-1>(k, at, mine, shift), right = run_side<1>(k, at, mine, shift);
+    int move = 0;
     if (left + right > RUN_MAX) {
       unsorted |= right > 0 && k[at + 1] < mine;
-      move = 0;
+    } else {
+#pragma unroll 4
+      for (int j = 1; j <= left; ++j) move -= k[at - j] > mine ? 1 : 0;
+#pragma unroll 4
+      for (int j = 1; j <= right; ++j) move += k[at + j] < mine ? 1 : 0;
     }
     vout[i + move] = val[it];
   }
@@ -464,11 +541,17 @@ __global__ void __launch_bounds__(FIX_THREADS) k_fix_runs(const uint64_t* __rest
 }
 
 // ----------------------------------------------------------------- gather
+// The kernels after the sort do nothing where it has raised its flag (unsorted):
+// the keys, the order so far and the input stay for the second sort, and the
+// host need not wait for the flag before it enqueues them.
+
 // Positions and colours of the input as one 16-byte record per point, in
 // input order: the gather then reads one record (one cache line) per output
 // instead of a position and a colour from two arrays.
 __global__ void __launch_bounds__(256) k_interleave(const float* __restrict__ xyz, const uint32_t* __restrict__ rgba,
-                                                    uint64_t n, uint4* __restrict__ rec) {
+                                                    uint64_t n, uint4* __restrict__ rec,
+                                                    const uint32_t* __restrict__ unsorted) {
+  if (*unsorted) return;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
     rec[i] = make_uint4(__float_as_uint(xyz[3 * i]), __float_as_uint(xyz[3 * i + 1]), __float_as_uint(xyz[3 * i + 2]),
@@ -491,12 +574,14 @@ __device__ __forceinline__ uint64_t spread_source(uint64_t i, const Spread& sp, 
 // Four consecutive outputs per thread: one 16-byte load of their sources, the
 // four record reads in flight together, 48 + 16 contiguous bytes written.
 // The outputs past the last multiple of four go one per thread.  SPREAD: the
-// sources come from the Morton positions of the spread order (perm_in), and
-// perm_out receives them.
+// sources come from the Morton positions of the spread order.  perm_out
+// receives the sources.
 template <bool SPREAD>
 __global__ void __launch_bounds__(256) k_gather(const uint4* __restrict__ rec, const uint32_t* __restrict__ perm,
                                                 uint32_t* __restrict__ perm_out, Spread sp, uint64_t n,
-                                                float* __restrict__ xyz_out, uint32_t* __restrict__ colors) {
+                                                float* __restrict__ xyz_out, uint32_t* __restrict__ colors,
+                                                const uint32_t* __restrict__ unsorted) {
+  if (*unsorted) return;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   const uint64_t n4 = n / 4;
   for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n4; g += stride) {
@@ -516,6 +601,7 @@ __global__ void __launch_bounds__(256) k_gather(const uint4* __restrict__ rec, c
       s[1] = p.y;
       s[2] = p.z;
       s[3] = p.w;
+      reinterpret_cast<uint4*>(perm_out)[g] = p;
     }
     uint4 r[4];
 #pragma unroll
@@ -534,10 +620,10 @@ __global__ void __launch_bounds__(256) k_gather(const uint4* __restrict__ rec, c
     if constexpr (SPREAD) {
       const uint64_t src = spread_source(i, sp, n);
       s = perm[src < n ? src : i];
-      perm_out[i] = (uint32_t)s;
     } else {
       s = perm[i];
     }
+    perm_out[i] = (uint32_t)s;
     if (s >= n) s = i;
     const uint4 r = rec[s];
     xyz_out[3 * i] = __uint_as_float(r.x);
@@ -549,9 +635,12 @@ __global__ void __launch_bounds__(256) k_gather(const uint4* __restrict__ rec, c
 
 // ------------------------------------------------------------ batch boxes
 // One block per batch: batch b is [b S, min((b + 1) S, n)), or, with spans,
-// [out[b].first, out[b].first + out[b].count) as set by the host.
+// [out[b].first, out[b].first + out[b].count) as set by the host.  unsorted: as
+// above, or null.
 __global__ void __launch_bounds__(256) k_batch_bbox(const float* __restrict__ xyz, uint64_t n, uint32_t S,
-                                                    BatchRec* __restrict__ out, int spans) {
+                                                    BatchRec* __restrict__ out, int spans,
+                                                    const uint32_t* __restrict__ unsorted) {
+  if (unsorted && *unsorted) return;
   const uint64_t first = spans ? out[blockIdx.x].first : (uint64_t)blockIdx.x * S;
   const uint64_t end = spans ? first + out[blockIdx.x].count : (first + S < n ? first + S : n);
   uint32_t mn[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, mx[3] = {0, 0, 0};
@@ -619,7 +708,9 @@ __device__ __forceinline__ Words3 eq1(const Axis (&ax)[3], float x, float y, flo
 
 __global__ void __launch_bounds__(256) k_quantize(const float* __restrict__ xyz, uint64_t n, uint32_t S,
                                                   const BatchRec* __restrict__ batches, uint32_t* __restrict__ low,
-                                                  uint32_t* __restrict__ med, uint32_t* __restrict__ high) {
+                                                  uint32_t* __restrict__ med, uint32_t* __restrict__ high,
+                                                  const uint32_t* __restrict__ unsorted) {
+  if (unsorted && *unsorted) return;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const BatchRec& B = batches[(uint32_t)i / S];  // i < 2^32
@@ -664,16 +755,18 @@ __global__ void __launch_bounds__(256) k_quantize_spans(const float* __restrict_
 // words.
 constexpr int WB_STEPS = 5;  // groups of four points per thread
 template <int ORDER, int THREADS>
-__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) k_batch(const float* __restrict__ xyz, const uint32_t* __restrict__ rgba,
-                                                   const uint4* __restrict__ rec, const uint32_t* __restrict__ order,
-                                                   Spread sp, uint64_t n, uint32_t S, float* __restrict__ xyz_out,
-                                                   uint32_t* __restrict__ colors, uint32_t* __restrict__ perm,
-                                                   BatchRec* __restrict__ batches, uint32_t* __restrict__ low,
-                                                   uint32_t* __restrict__ med, uint32_t* __restrict__ high,
-                                                   uint32_t* __restrict__ flag) {
+__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+k_batch(const float* __restrict__ xyz, const uint32_t* __restrict__ rgba, const uint4* __restrict__ rec,
+        const uint32_t* __restrict__ order, Spread sp, uint64_t n, uint32_t S, float* __restrict__ xyz_out,
+        uint32_t* __restrict__ colors, uint32_t* __restrict__ perm, BatchRec* __restrict__ batches,
+        uint32_t* __restrict__ low, uint32_t* __restrict__ med, uint32_t* __restrict__ high,
+        uint32_t* __restrict__ nonfinite, const uint32_t* __restrict__ unsorted) {
   __shared__ Box red[THREADS / 64];
   const uint64_t batch = xcd_tile(), first = batch * S;
   if (first >= n) return;
+  if constexpr (ORDER != 0) {
+    if (*unsorted) return;
+  }
   const uint32_t count = (uint32_t)(first + S <= n ? S : n - first);
   const uint32_t step = (uint32_t)(count == S ? sp.m : sp.m_last);
   float p[WB_STEPS][12];
@@ -756,7 +849,7 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
 #pragma unroll
     for (int j = 0; j < 12; ++j) grow(box, j % 3, p[k][j]);
   }
-  if constexpr (ORDER == 0) raise(flag, bad);
+  if constexpr (ORDER == 0) raise(nonfinite, bad);
   box = block_box(box, red);
   Axis ax[3];
 #pragma unroll
@@ -793,17 +886,6 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
         }
       }
     }
-  }
-}
-
-// Positions back from the records, for a second sort (xyz holds the gathered ones by then).
-__global__ void __launch_bounds__(256) k_restore(const uint4* __restrict__ rec, uint64_t n, float* __restrict__ xyz) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint4 r = rec[i];
-    xyz[3 * i] = __uint_as_float(r.x);
-    xyz[3 * i + 1] = __uint_as_float(r.y);
-    xyz[3 * i + 2] = __uint_as_float(r.z);
   }
 }
 
@@ -874,59 +956,58 @@ namespace {
 constexpr int FULL_PASSES = KEY_BITS / RS_BITS;  // every bit of the key
 static_assert(FULL_PASSES * RS_BITS == KEY_BITS, "whole passes");
 
-// The passes over the digits from bit 63 - 9 passes up; the first digit's
-// histogram is counted.  The values end in vals_last, the keys in the returned buffer.
-hipError_t radix_passes(const SortScratch& sc, uint64_t n, int passes, uint32_t* vals_last, uint32_t* vals_other,
-                        uint64_t** keys_out, hipStream_t s) {
+// Passes over the digits from bit 63 - 9 passes up, of the keys in kin and the values in vin (null: the indices, and
+// the first digit's histogram is counted already).  The values end in vals_last, the keys in kin or the other buffer.
+hipError_t radix_passes(const SortScratch& sc, uint64_t n, int passes, uint64_t* kin, const uint32_t* vin,
+                        uint32_t* vals_last, uint32_t* vals_other, hipStream_t s) {
   const uint64_t m = RS_DIGITS * sc.nblk;
-  uint64_t *kin = sc.keys0, *kout = sc.keys1;
-  const uint32_t* vin = nullptr;
   for (int p = 0; p < passes; ++p) {
     const int shift = KEY_BITS - RS_BITS * (passes - p);
+    uint64_t* const kout = kin == sc.keys0 ? sc.keys1 : sc.keys0;
     uint32_t* const vout = (passes - 1 - p) % 2 ? vals_other : vals_last;
-    if (p > 0)
+    if (vin)
       hipLaunchKernelGGL(k_radix_count, dim3((uint32_t)sc.nblk), dim3(RS_THREADS), 0, s, kin, n, shift, sc.hist, sc.nblk);
-    hipLaunchKernelGGL(k_scan_partials, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, sc.part, sc.npart);
-    hipLaunchKernelGGL(k_scan_apply, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
+    if (m <= SCAN_SMALL) {
+      hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(SS_THREADS), 0, s, sc.hist, m);
+    } else {
+      hipLaunchKernelGGL(k_scan_partials, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
+      hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, s, sc.part, sc.npart);
+      hipLaunchKernelGGL(k_scan_apply, dim3((uint32_t)sc.npart), dim3(256), 0, s, sc.hist, m, sc.part);
+    }
     hipLaunchKernelGGL(k_radix_scatter, dim3(xcd_grid(sc.nblk)), dim3(RS_THREADS), 0, s, kin, vin, kout, vout, n, shift,
                        sc.hist, sc.nblk);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    uint64_t* const t = kin;
     kin = kout;
-    kout = t;
     vin = vout;
   }
-  *keys_out = kin;
   return hipSuccess;
 }
+
+// Where the passes of the first sort leave its keys.
+uint64_t* sorted_keys(const SortScratch& sc, uint64_t n) { return sort_passes(n) % 2 ? sc.keys1 : sc.keys0; }
 }  // namespace
 
-hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, bool full,
-                              uint32_t* nonfinite, uint32_t* unsorted, hipStream_t s) {
+hipError_t launch_morton_sort(const SortScratch& sc, const float* xyz, uint32_t* perm, uint64_t n, uint32_t* nonfinite,
+                              uint32_t* unsorted, hipStream_t s) {
   if (n == 0) return hipSuccess;
   // the partial boxes lie in the second key buffer, not in use yet (24 bytes per 1,024 points, or one in 256)
   Box* const part = reinterpret_cast<Box*>(sc.keys1);
   const uint32_t blocks = grid_for(n, 1024, BOX_BLOCKS);
   hipLaunchKernelGGL(k_aabb, dim3(blocks), dim3(256), 0, s, xyz, n, part, nonfinite);
   hipLaunchKernelGGL(k_aabb_top, dim3(1), dim3(256), 0, s, part, blocks, sc.aabb);
-  const int passes = full ? FULL_PASSES : sort_passes(n), shift = KEY_BITS - RS_BITS * passes;
+  const int passes = sort_passes(n), shift = KEY_BITS - RS_BITS * passes;
   hipLaunchKernelGGL(k_morton, dim3((uint32_t)sc.nblk), dim3(RS_THREADS), 0, s, xyz, n, sc.aabb, sc.keys0, shift,
                      sc.hist, sc.nblk);
-  uint64_t* keys = nullptr;
-  hipError_t e;
-  if (full) return radix_passes(sc, n, passes, sc.vals1, perm, &keys, s);
-  if ((e = radix_passes(sc, n, passes, perm, sc.vals1, &keys, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fix_runs, dim3((uint32_t)((n + FIX_TILE - 1) / FIX_TILE)), dim3(FIX_THREADS), 0, s, keys, perm, n,
-                     shift, sc.vals1, unsorted);
+  const hipError_t e = radix_passes(sc, n, passes, sc.keys0, nullptr, perm, sc.vals1, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fix_runs, dim3((uint32_t)((n + FIX_TILE - 1) / FIX_TILE)), dim3(FIX_THREADS), 0, s,
+                     sorted_keys(sc, n), perm, n, shift, sc.vals1, unsorted);
   return hipGetLastError();
 }
 
-hipError_t launch_restore(const SortScratch& sc, uint64_t n, float* xyz, hipStream_t s) {
-  hipLaunchKernelGGL(k_restore, dim3(grid_for(n, 256 * 4)), dim3(256), 0, s, reinterpret_cast<const uint4*>(sc.keys0), n,
-                     xyz);
-  return hipGetLastError();
+hipError_t launch_morton_resort(const SortScratch& sc, uint32_t* perm, uint64_t n, hipStream_t s) {
+  return radix_passes(sc, n, FULL_PASSES, sorted_keys(sc, n), perm, sc.vals1, perm, s);
 }
 
 uint64_t spread_step(uint64_t c) {
@@ -958,7 +1039,7 @@ hipError_t launch_batch_t(const BuildArgs& a, const uint4* rec, const uint32_t* 
   const uint64_t nb = (a.n + a.S - 1) / a.S;
   hipLaunchKernelGGL((k_batch<ORDER, THREADS>), dim3(xcd_grid(nb)), dim3(THREADS), 0, s, a.xyz, a.rgba, rec, order,
                      ORDER == 2 ? make_spread(a.n, a.S) : Spread{}, a.n, a.S, a.xyz, a.colors, a.perm, a.batches, a.low,
-                     a.med, a.high, a.nonfinite);
+                     a.med, a.high, a.nonfinite, a.unsorted);
   return hipGetLastError();
 }
 template <int ORDER>
@@ -972,11 +1053,12 @@ hipError_t launch_batch(const BuildArgs& a, const uint4* rec, const uint32_t* or
 // kernels.
 bool whole_batches(uint32_t S) { return S >= 512 && S <= 1024u * 4 * WB_STEPS; }
 
-hipError_t boxes_and_words(const BuildArgs& a, hipStream_t s) {
+hipError_t boxes_and_words(const BuildArgs& a, const uint32_t* unsorted, hipStream_t s) {
   const uint64_t nb = (a.n + a.S - 1) / a.S;
-  hipError_t e = launch_batch_bbox(a.xyz, a.n, a.S, nb, a.batches, s);
-  if (e != hipSuccess) return e;
-  return launch_quantize(a.xyz, a.n, a.S, a.batches, a.low, a.med, a.high, s);
+  hipLaunchKernelGGL(k_batch_bbox, dim3((uint32_t)nb), dim3(256), 0, s, a.xyz, a.n, a.S, a.batches, 0, unsorted);
+  hipLaunchKernelGGL(k_quantize, dim3(grid_for(a.n, 256 * 4)), dim3(256), 0, s, a.xyz, a.n, a.S, a.batches, a.low, a.med,
+                     a.high, unsorted);
+  return hipGetLastError();
 }
 }  // namespace
 
@@ -986,7 +1068,7 @@ hipError_t launch_build_input(const BuildArgs& a, hipStream_t s) {
   hipError_t e = launch_finite_check(a.xyz, a.n, a.nonfinite, s);
   if (e == hipSuccess) e = launch_iota(a.perm, a.n, s);
   if (e == hipSuccess) e = hipMemcpyAsync(a.colors, a.rgba, 4 * a.n, hipMemcpyDeviceToDevice, s);
-  return e == hipSuccess ? boxes_and_words(a, s) : e;
+  return e == hipSuccess ? boxes_and_words(a, nullptr, s) : e;
 }
 
 hipError_t launch_build_sorted(const BuildArgs& a, const SortScratch& sc, bool spread, hipStream_t s) {
@@ -995,35 +1077,21 @@ hipError_t launch_build_sorted(const BuildArgs& a, const SortScratch& sc, bool s
   uint4* const rec = reinterpret_cast<uint4*>(sc.keys0);
   if (reinterpret_cast<uint8_t*>(sc.keys1) + 8 * a.n < reinterpret_cast<uint8_t*>(rec) + 16 * a.n) return hipErrorInvalidValue;
   const dim3 grid(grid_for(a.n, 256 * 4));
-  hipLaunchKernelGGL(k_interleave, grid, dim3(256), 0, s, a.xyz, a.rgba, a.n, rec);
+  hipLaunchKernelGGL(k_interleave, grid, dim3(256), 0, s, a.xyz, a.rgba, a.n, rec, a.unsorted);
   if (whole_batches(a.S)) return spread ? launch_batch<2>(a, rec, sc.vals1, s) : launch_batch<1>(a, rec, sc.vals1, s);
-  if (spread) {
+  if (spread)
     hipLaunchKernelGGL(k_gather<true>, grid, dim3(256), 0, s, rec, sc.vals1, a.perm, make_spread(a.n, a.S), a.n, a.xyz,
-                       a.colors);
-  } else {
-    const hipError_t e = hipMemcpyAsync(a.perm, sc.vals1, 4 * a.n, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gather<false>, grid, dim3(256), 0, s, rec, sc.vals1, a.perm, Spread{}, a.n, a.xyz, a.colors);
-  }
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? boxes_and_words(a, s) : e;
-}
-
-hipError_t launch_batch_bbox(const float* xyz, uint64_t n, uint32_t S, uint64_t nb, BatchRec* out, hipStream_t s) {
-  if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_bbox, dim3((uint32_t)nb), dim3(256), 0, s, xyz, n, S, out, 0);
-  return hipGetLastError();
-}
-
-hipError_t launch_quantize(const float* xyz, uint64_t n, uint32_t S, const BatchRec* batches, uint32_t* low,
-                           uint32_t* med, uint32_t* high, hipStream_t s) {
-  hipLaunchKernelGGL(k_quantize, dim3(grid_for(n, 256 * 4)), dim3(256), 0, s, xyz, n, S, batches, low, med, high);
-  return hipGetLastError();
+                       a.colors, a.unsorted);
+  else
+    hipLaunchKernelGGL(k_gather<false>, grid, dim3(256), 0, s, rec, sc.vals1, a.perm, Spread{}, a.n, a.xyz, a.colors,
+                       a.unsorted);
+  return boxes_and_words(a, a.unsorted, s);
 }
 
 hipError_t launch_batch_bbox_spans(const float* xyz, uint64_t nb, BatchRec* recs, hipStream_t s) {
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_bbox, dim3((uint32_t)nb), dim3(256), 0, s, xyz, (uint64_t)0, 0u, recs, 1);
+  hipLaunchKernelGGL(k_batch_bbox, dim3((uint32_t)nb), dim3(256), 0, s, xyz, (uint64_t)0, 0u, recs, 1,
+                     (const uint32_t*)nullptr);
   return hipGetLastError();
 }
 

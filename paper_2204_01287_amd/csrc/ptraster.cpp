@@ -434,20 +434,22 @@ pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, in
     a.med = static_cast<uint32_t*>(B.med);
     a.high = static_cast<uint32_t*>(B.high);
     a.nonfinite = flags;
+    a.unsorted = flags + 1;
     if (morton) {
       ptr::SortScratch sc;
       ptr::sort_scratch_layout(n, static_cast<uint8_t*>(B.scratch), &sc);
       if (sc.end > ptr::small_scratch_bytes() + ptr::sort_scratch_bytes(n))
         return fail(PR_EINVAL, "pr_build_batches: the sort areas exceed the scratch buffer");
       const bool spread = morton == PR_ORDER_MORTON_SPREAD;
-      for (bool full : {false, true}) {
-        if (full) HIP_TRY(ptr::launch_restore(sc, n, a.xyz, st), "positions of the input order");
-        HIP_TRY(ptr::launch_morton_sort(sc, a.xyz, a.perm, n, full, flags, flags + 1, st), "Morton sort");
+      HIP_TRY(ptr::launch_morton_sort(sc, a.xyz, a.perm, n, a.nonfinite, a.unsorted, st), "Morton sort");
+      HIP_TRY(ptr::launch_build_sorted(a, sc, spread, st), "batches");
+      if (pr_status s = read_flags(ctx, seen)) return s;
+      // a run of points that the sort's leading bits leave equal, too long for the short way and out of order (a dense
+      // spot, a few points far from all others): the batches were not made, and the order is finished over every bit
+      if (!seen[0] && seen[1]) {
+        HIP_TRY(ptr::launch_morton_resort(sc, a.perm, n, st), "Morton sort of every bit");
         HIP_TRY(ptr::launch_build_sorted(a, sc, spread, st), "batches");
-        if (pr_status s = read_flags(ctx, seen)) return s;
-        // a run of points that the sort's leading bits leave equal, too long for the short way and out of
-        // order (a few points far from all others): again with every bit
-        if (seen[0] || !seen[1]) break;
+        HIP_TRY(hipStreamSynchronize(st), "build");
       }
     } else {
       HIP_TRY(ptr::launch_build_input(a, st), "batches");
