@@ -61,6 +61,7 @@ struct Loop {
   uint32_t tw8;     // tile row pitch in bytes
   uint32_t base8;   // byte offset of this view's sub-tile in the LDS tile (two-view passes)
   uint64_t* vb;
+  bool solo;        // untiled batches: one early-depth read in flight at a time (read_alone)
   // high-quality shading pass only
   float window;     // depth window factor
   uint64_t* acc;    // global sums, two words per pixel
@@ -218,52 +219,6 @@ __device__ __forceinline__ void four_points_acc(const Loop& L, uint64_t* tile, c
   }
 }
 
-// Four consecutive points of one lane straight into the visibility buffer, in
-// two steps: keys and early-depth reads, then the atomics of the keys that beat
-// them.
-struct Direct {
-  uint32_t off[4];
-  uint64_t key[4], old[4];  // old: 0 where nothing is to be written
-};
-template <int K, int CLS>
-__device__ __forceinline__ void direct_read(const Loop& L, const Words& w, uint32_t i0, uint32_t nvalid, Direct& q) {
-  const uint32_t Lw[4] = {w.l.x, w.l.y, w.l.z, w.l.w};
-  const uint32_t Mw[4] = {w.m.x, w.m.y, w.m.z, w.m.w};
-  const uint32_t Hw[4] = {w.h.x, w.h.y, w.h.z, w.h.w};
-  bool ok[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float X, Y, Z;
-    decode<K>(Lw[j], Mw[j], Hw[j], X, Y, Z);
-    const Proj p = project(L, X, Y, Z);
-    ok[j] = (uint32_t)j < nvalid;
-    if constexpr (CLS != CLS_INSIDE) ok[j] = ok[j] && visible(L, p);
-    uint32_t px, py;
-    if constexpr (CLS == CLS_SLOW)
-      pixel_exact(p, px, py);
-    else
-      pixel_fast(p, L.cx, L.cy, px, py);
-    // Never address outside the image, whatever the class proofs say.
-    ok[j] = ok[j] && (px < L.W) && (py < L.H);
-    q.off[j] = __umul24(py, L.W) + px;
-    q.key[j] = make_key(p.hw, i0 + j);
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    q.old[j] = 0;
-    if (ok[j]) q.old[j] = __hip_atomic_load(L.vb + q.off[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  }
-}
-__device__ __forceinline__ void direct_write(const Loop& L, const Direct& q, uint32_t& natom) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (q.key[j] < q.old[j]) {
-      __hip_atomic_fetch_min(L.vb + q.off[j], q.key[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      natom++;
-    }
-  }
-}
-
 // Four consecutive points of one lane.
 // BAND (tiled path only): the tile covers one band of rows of the batch's
 // rectangle (L.th rows from the band origin); points of other rows are
@@ -325,9 +280,52 @@ __device__ __forceinline__ void four_points(const Loop& L, uint64_t* tile, const
         __hip_atomic_fetch_min(reinterpret_cast<uint64_t*>(tb + ad[j]), key[j], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
   } else {
-    Direct q;
-    direct_read<K, CLS>(L, w, i0, nvalid, q);
-    direct_write(L, q, natom);
+    uint32_t off[4];
+    uint64_t key[4];
+    bool ok[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float X, Y, Z;
+      decode<K>(Lw[j], Mw[j], Hw[j], X, Y, Z);
+      const Proj p = project(L, X, Y, Z);
+      ok[j] = (uint32_t)j < nvalid;
+      if constexpr (CLS != CLS_INSIDE) ok[j] = ok[j] && visible(L, p);
+      uint32_t px, py;
+      if constexpr (CLS == CLS_SLOW)
+        pixel_exact(p, px, py);
+      else
+        pixel_fast(p, L.cx, L.cy, px, py);
+      // Never address outside the image, whatever the class proofs say.
+      ok[j] = ok[j] && (px < L.W) && (py < L.H);
+      off[j] = __umul24(py, L.W) + px;
+      key[j] = make_key(p.hw, i0 + j);
+    }
+    // all early-depth reads first, then the atomics
+    const auto read = [&](int j) {
+      return __hip_atomic_load(L.vb + off[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    };
+    if (L.solo) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (ok[j]) ok[j] = key[j] < read(j);  // compared here: the wave waits for the read before the next one
+      }
+    } else {
+      uint64_t old[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        old[j] = 0;
+        if (ok[j]) old[j] = read(j);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ok[j] = ok[j] && key[j] < old[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (ok[j]) {
+        __hip_atomic_fetch_min(L.vb + off[j], key[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        natom++;
+      }
+    }
   }
 }
 
@@ -580,66 +578,8 @@ __device__ __forceinline__ void stream_chunk(const Streams& a, uint32_t first, u
   }
 }
 
-// The groups of a chunk in pairs, for the untiled path: both groups' early-depth
-// reads are in flight before the first atomic, so a wave waits for half as many
-// round trips (a full batch's ten groups: five; 352 -> 346 us a frame at 1e9
-// points and 2016x2240, 142 -> 138 at 1e8 and 1920x1080; an odd last group is
-// worked alone: projecting it as a pair's empty half took the gain back).  Not in the multi-view
-// kernel: no gain there (64 views of 5e8 points: 5.25 ms with it, 5.20 without).  Same distribution of
-// groups and tail as stream_chunk.
-template <int K, int CLS>
-__device__ __forceinline__ void direct_chunk(const Loop& L, const Streams& a, uint32_t first, uint32_t count,
-                                             uint32_t wave, uint32_t lane, uint32_t& natom) {
-  const BatchStreams bs = batch_streams<K, false>(a, first);
-  const uint32_t lane16 = lane * 16u;
-  const uint32_t ngrp = count >> 8;
-  const uint32_t nj = wave < ngrp ? (ngrp - wave + WAVES - 1) / WAVES : 0;
-  constexpr int PF = K == 10 ? 4 : 2;
-  if (nj > 0) {
-    const uint32_t glast = wave + (nj - 1) * WAVES;
-    Words R[PF];
-    uint32_t gi[PF];
-#pragma unroll
-    for (int d = 0; d < PF; ++d) {
-      gi[d] = wave + d * WAVES;
-      R[d] = load_group<K, false>(bs, min(gi[d], glast), lane16);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    for (uint32_t left = nj;; left -= PF) {
-#pragma unroll
-      for (int d = 0; d < PF; d += 2) {
-        if ((uint32_t)d < left) {
-          Direct q0, q1;
-          direct_read<K, CLS>(L, R[d], first + gi[d] * 256 + lane * 4, 4u, q0);
-          if ((uint32_t)d + 1 < left) {
-            direct_read<K, CLS>(L, R[d + 1], first + gi[d + 1] * 256 + lane * 4, 4u, q1);
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) q1.key[j] = q1.old[j] = 0;
-          }
-          gi[d] += PF * WAVES;
-          gi[d + 1] += PF * WAVES;
-          if (left > PF) {
-            R[d] = load_group<K, false>(bs, min(gi[d], glast), lane16);
-            R[d + 1] = load_group<K, false>(bs, min(gi[d + 1], glast), lane16);
-          }
-          direct_write(L, q0, natom);
-          direct_write(L, q1, natom);
-        }
-      }
-      if (left <= PF) break;
-    }
-  }
-  const uint32_t rem = count & 255u;
-  if (rem && wave == ngrp % WAVES)  // the ragged tail alone
-    stream_chunk<K, false, 1>(a, first + ngrp * 256u, rem, 0, lane, [&](const Words& w, uint32_t i0, uint32_t nv) {
-      four_points<K, CLS, false>(L, nullptr, w, i0, nv, natom);
-    });
-}
-
 // The points of one batch into one view (tile or visibility buffer).
-// PAIRS: the untiled loops of the single-view kernel (direct_chunk).
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
                                              uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
                                              Pre&& pre = Pre()) {
@@ -647,10 +587,6 @@ __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, ui
   // rare 20- and 30-bit batches (two and three words per point) at most
   // three: deeper prefetch there would set the register count of the whole
   // kernel, which the 10-bit loops (almost every point) then pay for.
-  if constexpr (PAIRS && !TILED && !ACC && CLS != CLS_SLOW) {
-    direct_chunk<K, CLS>(L, a, first, count, wave, lane, natom);
-    return;
-  }
   constexpr int PF = CLS == CLS_SLOW ? 1 : (K == 10 ? PREFETCH : (PREFETCH < 3 ? PREFETCH : 3));
   stream_chunk<K, ACC, PF>(
       a, first, count, wave, lane,
@@ -662,13 +598,13 @@ __device__ __forceinline__ void raster_chunk(const Loop& L, const Streams& a, ui
 
 // A batch, in chunks of at most CHUNK_POINTS points (one chunk for every
 // batch of a regular build).  pre() as in stream_chunk, once unless count is 0.
-template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
+template <int K, int CLS, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_points(const Loop& L, const Streams& a, uint64_t* tile, uint32_t first,
                                               uint32_t count, uint32_t wave, uint32_t lane, uint32_t& natom,
                                               Pre&& pre = Pre()) {
   for (uint32_t c0 = 0; c0 < count; c0 += CHUNK_POINTS) {
     const uint32_t n = count - c0 < CHUNK_POINTS ? count - c0 : CHUNK_POINTS;
-    raster_chunk<K, CLS, TILED, ACC, BAND, PAIRS>(L, a, tile, first + c0, n, wave, lane, natom, [&] {
+    raster_chunk<K, CLS, TILED, ACC, BAND>(L, a, tile, first + c0, n, wave, lane, natom, [&] {
       if (c0 == 0) pre();
     });
   }
@@ -686,14 +622,14 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
 
 
 // ------------------------------------------------------------------ render
-template <int K, bool TILED, bool ACC = false, bool BAND = false, bool PAIRS = false, typename Pre = Nothing>
+template <int K, bool TILED, bool ACC = false, bool BAND = false, typename Pre = Nothing>
 __device__ __forceinline__ void raster_by_class(int cls, const Loop& L, const Streams& a, uint64_t* tile,
                                                 uint32_t first, uint32_t count, uint32_t wave, uint32_t lane,
                                                 uint32_t& natom, Pre&& pre = Pre()) {
   if (cls == CLS_INSIDE)
-    raster_points<K, CLS_INSIDE, TILED, ACC, BAND, PAIRS>(L, a, tile, first, count, wave, lane, natom, pre);
+    raster_points<K, CLS_INSIDE, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
   else if (cls == CLS_PARTIAL)
-    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND, PAIRS>(L, a, tile, first, count, wave, lane, natom, pre);
+    raster_points<K, CLS_PARTIAL, TILED, ACC, BAND>(L, a, tile, first, count, wave, lane, natom, pre);
   else if constexpr (!TILED)
     raster_points<K, CLS_SLOW, false, ACC>(L, a, tile, first, count, wave, lane, natom);
 }
@@ -791,6 +727,20 @@ __device__ __forceinline__ Span banded_part(Span b, uint32_t th, uint32_t bh, ui
   return y0 < y1 ? points_part(b, slice % parts, parts) : Span{b.first, 0u};
 }
 
+// Whether the untiled loops of a frame of as many batches as workgroups, or
+// more, keep one early-depth read of a wave in flight instead of four.  Where the
+// visibility buffer is several times an XCD's 4 MiB of L2, most reads miss it and
+// more of them at once only hold up the atomics (us a frame with four and with one:
+// kernel, 1e9 points at 2016x2240, 361 and 349; 1e8 at 1920x1080, 30 bits, 360 and
+// 343, 10 bits, 141 and 142; pass, 5e7 at 2382x1923, 20 bits, 416 and 337).  In
+// smaller images four hide each other's latency (pass, 2.5e7 points of 20 bits in
+// batches that cover each other, 1280x720, 446 and 493), and so they do at any size
+// where the batches leave workgroups idle (4.6e6 points of 20 bits: one is 3-5 %
+// slower).  Eight, of two groups of points, before the first atomic come too early:
+// up to 2.5 times as many atomics where batches cover each other, 1e7 points of
+// 20 bits at 1280x720 367 us against 267.
+__device__ __forceinline__ bool read_alone(uint32_t W, uint32_t H) { return W * H > (1u << 20); }
+
 // One live batch of one view by the whole workgroup: its points into the LDS
 // tile (or straight into the global buffer), then the tile flush.  The LDS
 // tile is all PR_EMPTY between batches (the flush resets what it reads), so a
@@ -799,12 +749,12 @@ __device__ __forceinline__ Span banded_part(Span b, uint32_t th, uint32_t bh, ui
 // points once per band of rows that fits the tile, with the same two barriers
 // per band.  publish: thread 0 stores next into s_next after the first
 // barrier (the workgroup reads it after the last one).  slice, shift: the part
-// of the batch to render (above; shift 0: all of it).
-template <bool PAIRS>
+// of the batch to render (above; shift 0: all of it).  whole: the frame has as
+// many batches as workgroups, or more.
 __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, uint32_t H, uint64_t* vb,
                                              const Streams& st, uint64_t* tile, uint32_t tid, uint32_t wave,
                                              uint32_t lane, bool publish, uint32_t next, uint32_t* s_next,
-                                             uint32_t slice, uint32_t shift, uint32_t& natom) {
+                                             uint32_t slice, uint32_t shift, bool whole, uint32_t& natom) {
   Loop L;
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
@@ -815,6 +765,7 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   L.W = W;
   L.H = H;
   L.vb = vb;
+  L.solo = whole && read_alone(W, H);
   const uint32_t mode = rec.mode, rxy = rec.rect_xy, rwh = rec.rect_wh;
   Span b = {rec.first, rec.count};
   const uint32_t x0 = rxy & 0xFFFFu, y0 = rxy >> 16;
@@ -859,9 +810,9 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
     else if (k == 20) raster_by_class<20, true>(cls, L, st, tile, first, count, wave, lane, natom);
     else raster_by_class<30, true>(cls, L, st, tile, first, count, wave, lane, natom);
   } else {
-    if (k == 10) raster_by_class<10, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
-    else if (k == 20) raster_by_class<20, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
-    else raster_by_class<30, false, false, false, PAIRS>(cls, L, st, tile, first, count, wave, lane, natom);
+    if (k == 10) raster_by_class<10, false>(cls, L, st, tile, first, count, wave, lane, natom);
+    else if (k == 20) raster_by_class<20, false>(cls, L, st, tile, first, count, wave, lane, natom);
+    else raster_by_class<30, false>(cls, L, st, tile, first, count, wave, lane, natom);
   }
   __syncthreads();  // the batch's points are all in the tile; s_next has been read
   if (publish && tid == 0) *s_next = next;
@@ -1033,7 +984,8 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
     // Take the next position now; the atomic's latency hides behind this batch.
     uint32_t grab = 0;
     if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-    render_batch<true>(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift, natom);
+    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift,
+                 nt + nd >= gridDim.x, natom);
     p = uni(s_next);
     i = live_slot(p >> shift, nt, nd, rate, a.nb);
   }
@@ -1085,7 +1037,8 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
         }
       }
       const ViewOut& vo = a.v[v];
-      render_batch<false>(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift, natom);
+      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift,
+                   nt + nd >= gridDim.x, natom);
       publish = false;
     }
     p = uni(s_next);
