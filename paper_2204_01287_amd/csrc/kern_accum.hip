@@ -84,18 +84,17 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
   // batch order (Morton order for sorted clouds): the sums' lines of neighbouring
   // batches stay in the caches; measured faster than the render's order here
   const uint32_t nlive = a.hdr->live_count + a.hdr->direct_count;
-  const uint32_t shift = slice_shift(nlive, a.hdr->direct_count, gridDim.x);
-  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+  const Cut cut = cut_of(nlive);
   for (uint32_t e = tid; e < 2 * HQS_TILE; e += THREADS) sums[e] = 0;
   const Streams st = {a.low, a.med, a.high, a.colors};
   __syncthreads();
-  uint32_t p = uni(s_next);
+  uint32_t item, slice;
+  cut.at(first_position(cut, qc, q, &s_next), item, slice);
   uint32_t natom = 0;
-  while (p >> shift < nlive) {
-    const uint32_t slice = p & ((1u << shift) - 1u);
+  while (item < nlive) {
     uint32_t grab = 0;
-    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-    const LiveBatch& rec = a.live[uni(a.order[p >> shift])];
+    if (tid == 0) grab = next_position(cut, qc, q);
+    const LiveBatch& rec = a.live[uni(a.order[item])];
     Loop L;
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -124,8 +123,8 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     if (banded) {
       const uint32_t bh = HQS_TILE / L.tw;
       uint32_t by0 = 0, by1 = L.th;
-      if (shift) {
-        b = banded_part({uni(b.first), uni(b.count)}, uni(L.th), bh, slice, shift, by0, by1);
+      if (cut.shift) {
+        b = banded_part({uni(b.first), uni(b.count)}, uni(L.tw), uni(L.th), bh, slice, cut, by0, by1);
         if (b.count == 0) {  // nothing in this slice
           by0 = 0;
           by1 = 1;
@@ -145,12 +144,12 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
         flush_band(a, sums, tid, x0, y0 + by, L.tw, L.th);
         __syncthreads();  // tile free again
       }
-      p = uni(s_next);
+      cut.at(uni(s_next), item, slice);
       continue;
     }
-    if (shift) {
+    if (cut.shift) {
       b = {uni(b.first), uni(b.count)};
-      b = tiled ? tiled_part(b, uni(n), slice, shift) : points_part(b, slice, 1u << shift);
+      b = tiled ? tiled_part(b, uni(n), slice, cut.shift) : points_part(b, slice, 1u << cut.shift);
     }
     const uint32_t first = b.first, count = b.count;
     L.cx = in_vgpr(uni(0x4B000000u + (tiled ? x0 : 0u)));
@@ -171,9 +170,9 @@ __global__ void __launch_bounds__(THREADS) k_accum(RenderArgs a) {
     }
     __syncthreads();  // the batch's sums are complete; s_next has been read
     if (tid == 0) s_next = grab;
-    if (tiled) flush_band(a, sums, tid, x0, y0, L.tw, L.th);
+    if (tiled && count != 0) flush_band(a, sums, tid, x0, y0, L.tw, L.th);
     __syncthreads();  // tile free for the next batch; s_next visible
-    p = uni(s_next);
+    cut.at(uni(s_next), item, slice);
   }
 }
 

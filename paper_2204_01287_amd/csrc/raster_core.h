@@ -668,33 +668,59 @@ __device__ __forceinline__ void flush_tile(uint64_t* tile, uint32_t tid, uint64_
 
 // Slices.  A frame of fewer live batches than workgroups would leave most of
 // the chip idle behind one long chain of loads per batch, so each batch is cut
-// into 1 << shift queue items, enough for two per workgroup and 16 at most
-// (finer ones lose more to further flushes than the idle workgroups give: 1e6
-// points in 98 batches 46 us at 32 slices against 40 at 16).  Slice s of a
-// batch takes a share of its points, in whole groups of 256 (the smallest work
-// of a wave).  A tiled batch stays in as few parts as keep the flushes (one of
-// the whole rectangle per part) below the work on the points; a banded one
-// deals out its bands first, so that a part streams its points for one band
-// only.  Slices without a part do nothing.  Frames of as many batches as
-// workgroups or more are not cut: slices of their last batches alone gained
-// nothing.  Nor are frames of many untiled batches: an eighth as many as there are
-// workgroups keep the device's atomics busy by themselves, and more waves at
-// once only read the buffer earlier and write more (205 untiled batches of 2e6
-// points at 2382x1923: kernel 66 us uncut, 72 in 16 slices, 70 in 2; 98 batches
-// of 1e6 at 1280x720: 45 uncut, 39 in 16).  Pass times, before and after: 2e4 points at 641x479 51 -> 18 us,
-// 2e5 at 2116x1607 37 -> 21, 1e6 at 1280x720 60 -> 50, shading of 1.2e5 points
-// at 1206x751 150 -> 39.
-__device__ __forceinline__ uint32_t slice_shift(uint32_t items, uint32_t untiled, uint32_t grid) {
-  uint32_t shift = 0;
-  while (shift < MAX_SLICE_SHIFT && (items << shift) < 2u * grid) ++shift;
-  return items < grid && untiled < grid * WAVES / 32u ? shift : 0u;  // grids of four-wave workgroups: an eighth
+// into 1 << shift slices, two to four per workgroup and 16 at most, and the queue
+// holds them slice by slice: position p is slice p / items of batch p mod items.
+// Slice s of a batch takes a share of its points, in whole groups of 256 (the
+// smallest work of a wave).  A tiled batch stays in as few parts as keep the
+// flushes (one of the whole rectangle per part) below the work on the points; a
+// banded one deals out its bands, so that a part streams its points for one band
+// only, and its points too where workgroups would stay idle or a band has
+// twice as many points as pixels.  Slices without a part do nothing.  Every live
+// batch is cut, whatever its kind: the band limit (tune_bands in ptraster.cpp)
+// counts on it.
+//
+// Passes of pr_render without slices, with them in frames of few untiled batches
+// only and batch by batch, and now (us): 1e6 points of overlapping batches at 1280x720
+// 59, 43, 34; a terrain of 2.1e6 points at 1280x720 38, 82, 32, of 1.3e6 at 2382x1923
+// 57, 114, 50, of 1e7 141, 135, 118; 1e6 at 20 bits, untiled, 40, 40, 33; shading of
+// 2.1e6 points 109, 178, 80; three views of them in one launch 95, 89, 70.  Where
+// batches cover each other and all are untiled, slices write more than they save (2.1e6
+// points of 20 bits at 1280x720: 85, 79, 93; uncut at more than 128 workgroups they take
+// 77, but terrains then 53 instead of 42).  Half as many slices are slower by 3 % over
+// 600 such frames, limits on the untiled ones' by 4-7 %.
+struct Cut {
+  uint32_t items;  // live batches (or runs) of the frame
+  uint32_t shift;  // slices of a batch: 1 << shift
+  bool whole;      // as many batches as workgroups, or more: not cut
+  // Whether the slices occupy every workgroup.
+  __device__ __forceinline__ bool full() const { return items << shift >= gridDim.x; }
+  // The batch (an index below items, or past the end) and the slice of queue position p.
+  __device__ __forceinline__ void at(uint32_t p, uint32_t& item, uint32_t& slice) const {
+    slice = shift ? p / items : 0u;
+    item = slice >> shift ? ~0u : p - slice * items;
+  }
+};
+__device__ __forceinline__ Cut cut_of(uint32_t items) {
+  Cut c = {items, 0, items >= gridDim.x};
+  if (items != 0 && !c.whole)
+    while (c.shift < MAX_SLICE_SHIFT && (items << c.shift) < 2u * gridDim.x) ++c.shift;
+  return c;
 }
-// Uncut frames of fewer batches than workgroups: one workgroup per batch (and one
-// per queue at least) stays, in launch order, so that the batches lie on as many
-// CUs as there are; left to all, the first workgroups of a CU took several.
-__device__ __forceinline__ bool surplus(uint32_t items, uint32_t shift) {
-  return shift == 0 && blockIdx.x >= items && blockIdx.x >= RENDER_QUEUES && items < gridDim.x &&
-         blockIdx.x >= (items + RENDER_QUEUES - 1) / RENDER_QUEUES * RENDER_QUEUES;
+// Queue positions.  In a frame that is cut a workgroup's first is its index in the
+// launch: no workgroup takes a second item before each has one, and those of a small
+// frame lie on as many CUs as there are.  The later ones come from the counter of its
+// queue (blockIdx mod RENDER_QUEUES).  In whole frames all do: their untiled batches lie at
+// even distances, which the order of launch can turn into the same few CUs (170 among
+// 1,500 of 20 bits at 1280x720: 146 us, 112 by tickets).
+__device__ __forceinline__ uint32_t next_position(const Cut& cut, uint32_t* counter, uint32_t q) {
+  const uint32_t taken = cut.whole ? 0u : (gridDim.x - q + RENDER_QUEUES - 1u) / RENDER_QUEUES;
+  return (atomicAdd(counter, 1u) + taken) * RENDER_QUEUES + q;
+}
+__device__ __forceinline__ uint32_t first_position(const Cut& cut, uint32_t* counter, uint32_t q, uint32_t* s_next) {
+  if (!cut.whole) return blockIdx.x;
+  if (threadIdx.x == 0) *s_next = next_position(cut, counter, q);
+  __syncthreads();
+  return uni(*s_next);
 }
 struct Span {
   uint32_t first, count;
@@ -711,18 +737,19 @@ __device__ __forceinline__ Span tiled_part(Span b, uint32_t area, uint32_t slice
   while (parts > 1u && (uint64_t)parts * area > 4ull * b.count) parts >>= 1;
   return points_part(b, slice, parts);
 }
-// The part of a banded batch of rows th in bands of bh: its points and its rows [y0, y1).
-__device__ __forceinline__ Span banded_part(Span b, uint32_t th, uint32_t bh, uint32_t slice, uint32_t shift,
+// The part of a banded batch of rows th and tw pixels a row in bands of bh rows: its points and its rows [y0, y1).
+__device__ __forceinline__ Span banded_part(Span b, uint32_t tw, uint32_t th, uint32_t bh, uint32_t slice, const Cut& cut,
                                             uint32_t& y0, uint32_t& y1) {
-  const uint32_t k = 1u << shift, bands = (th + bh - 1u) / bh;
+  const uint32_t k = 1u << cut.shift, bands = (th + bh - 1u) / bh;
   if (bands >= k) {
     const uint32_t per = (bands + k - 1u) / k * bh;
     y0 = min(slice * per, th);
     y1 = min(y0 + per, th);
     return y0 < y1 ? b : Span{b.first, 0u};
   }
-  const uint32_t parts = k / bands, band = slice / parts;
-  y0 = min(band * bh, th);
+  uint32_t parts = k / bands;
+  while (cut.full() && parts > 1u && 2ull * parts * tw * bh > b.count) --parts;
+  y0 = min(slice / parts * bh, th);
   y1 = min(y0 + bh, th);
   return y0 < y1 ? points_part(b, slice % parts, parts) : Span{b.first, 0u};
 }
@@ -748,13 +775,12 @@ __device__ __forceinline__ bool read_alone(uint32_t W, uint32_t H) { return W * 
 // banded batch (rectangle up to a few tiles, at most one tile wide) streams its
 // points once per band of rows that fits the tile, with the same two barriers
 // per band.  publish: thread 0 stores next into s_next after the first
-// barrier (the workgroup reads it after the last one).  slice, shift: the part
-// of the batch to render (above; shift 0: all of it).  whole: the frame has as
-// many batches as workgroups, or more.
+// barrier (the workgroup reads it after the last one).  slice, cut: the part
+// of the batch to render (above).
 __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, uint32_t H, uint64_t* vb,
                                              const Streams& st, uint64_t* tile, uint32_t tid, uint32_t wave,
                                              uint32_t lane, bool publish, uint32_t next, uint32_t* s_next,
-                                             uint32_t slice, uint32_t shift, bool whole, uint32_t& natom) {
+                                             uint32_t slice, const Cut& cut, uint32_t& natom) {
   Loop L;
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
@@ -765,7 +791,7 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   L.W = W;
   L.H = H;
   L.vb = vb;
-  L.solo = whole && read_alone(W, H);
+  L.solo = cut.whole && read_alone(W, H);
   const uint32_t mode = rec.mode, rxy = rec.rect_xy, rwh = rec.rect_wh;
   Span b = {rec.first, rec.count};
   const uint32_t x0 = rxy & 0xFFFFu, y0 = rxy >> 16;
@@ -777,8 +803,8 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
   if ((mode >> 17) & 1u) {
     const uint32_t bh = TILE_MAX / L.tw;  // rows per band (the rectangle is at most one tile wide)
     uint32_t by0 = 0, by1 = L.th;
-    if (shift) {
-      b = banded_part({uni(b.first), uni(b.count)}, uni(L.th), bh, slice, shift, by0, by1);
+    if (cut.shift) {
+      b = banded_part({uni(b.first), uni(b.count)}, uni(L.tw), uni(L.th), bh, slice, cut, by0, by1);
       if (b.count == 0) {  // nothing in this slice
         by0 = 0;
         by1 = 1;
@@ -798,9 +824,9 @@ __device__ __forceinline__ void render_batch(const LiveBatch& rec, uint32_t W, u
     }
     return;
   }
-  if (shift) {
+  if (cut.shift) {
     b = {uni(b.first), uni(b.count)};
-    b = tiled ? tiled_part(b, uni(L.tw * L.th), slice, shift) : points_part(b, slice, 1u << shift);
+    b = tiled ? tiled_part(b, uni(L.tw * L.th), slice, cut.shift) : points_part(b, slice, 1u << cut.shift);
   }
   const uint32_t first = b.first, count = b.count;
   L.cx = in_vgpr(uni(0x4B000000u + (tiled ? x0 : 0u)));
@@ -862,14 +888,14 @@ constexpr int PAIR_PF = PREFETCH < 3 ? PREFETCH : 3;
 __device__ __forceinline__ void render_pair(const LiveBatch& ra, const ViewOut& va, const LiveBatch& rb,
                                             const ViewOut& vb, const Streams& st, uint64_t* tile, uint32_t tid,
                                             uint32_t wave, uint32_t lane, bool publish, uint32_t next,
-                                            uint32_t* s_next, uint32_t slice, uint32_t shift, uint32_t& natom) {
+                                            uint32_t* s_next, uint32_t slice, const Cut& cut, uint32_t& natom) {
   const Loop A = tiled_loop(ra, va.W, va.H, va.vb);
   Loop B = tiled_loop(rb, vb.W, vb.H, vb.vb);
   const uint32_t na = uni(rect_area(ra));
   B.base8 = na * 8u;
   // uniform by construction (one record per workgroup); said so for the compiler
   Span part = {uni(ra.first), uni(ra.count)};
-  if (shift) part = tiled_part(part, na + uni(rect_area(rb)), slice, shift);
+  if (cut.shift) part = tiled_part(part, na + uni(rect_area(rb)), slice, cut.shift);
   const uint32_t first = part.first, count = part.count;
   const int ca = (int)((uni(ra.mode) >> 8) & 0xFFu), cb = (int)((uni(rb.mode) >> 8) & 0xFFu);
   // y and w rows bit-equal in both records: shared chains
@@ -973,21 +999,20 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
-  if (surplus(nt + nd, shift)) return;
-  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+  const Cut cut = cut_of(nt + nd);
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
-  uint32_t p = uni(s_next), i = live_slot(p >> shift, nt, nd, rate, a.nb);
+  uint32_t item, slice;
+  cut.at(first_position(cut, qc, q, &s_next), item, slice);
+  uint32_t i = live_slot(item, nt, nd, rate, a.nb);
   uint32_t natom = 0;
   while (i != ~0u) {
     // Take the next position now; the atomic's latency hides behind this batch.
     uint32_t grab = 0;
-    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
-    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, p & in_batch, shift,
-                 nt + nd >= gridDim.x, natom);
-    p = uni(s_next);
-    i = live_slot(p >> shift, nt, nd, rate, a.nb);
+    if (tid == 0) grab = next_position(cut, qc, q);
+    render_batch(a.live[i], a.W, a.H, a.vb, st, tile, tid, wave, lane, true, grab, &s_next, slice, cut, natom);
+    cut.at(uni(s_next), item, slice);
+    i = live_slot(item, nt, nd, rate, a.nb);
   }
   add_atomics<CNT>(a.stats, natom, lane);
 }
@@ -1005,16 +1030,16 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
   const uint32_t q = blockIdx.x % RENDER_QUEUES;
   uint32_t* const qc = &a.hdr->queue[q][0];
   const uint32_t nt = a.hdr->live_count, nd = a.hdr->direct_count, rate = spread_rate(nt, nd);
-  const uint32_t shift = slice_shift(nt + nd, nd, gridDim.x), in_batch = (1u << shift) - 1u;
-  if (surplus(nt + nd, shift)) return;
-  if (tid == 0) s_next = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+  const Cut cut = cut_of(nt + nd);
   const Streams st = {a.low, a.med, a.high, nullptr};
   __syncthreads();
-  uint32_t p = uni(s_next), i = live_slot(p >> shift, nt, nd, rate, a.cap);
+  uint32_t item, slice;
+  cut.at(first_position(cut, qc, q, &s_next), item, slice);
+  uint32_t i = live_slot(item, nt, nd, rate, a.cap);
   uint32_t natom = 0;
   while (i != ~0u) {
     uint32_t grab = 0;
-    if (tid == 0) grab = atomicAdd(qc, 1u) * RENDER_QUEUES + q;
+    if (tid == 0) grab = next_position(cut, qc, q);
     const Run run = a.runs[i];
     uint64_t mask = run.mask;
     bool publish = true;
@@ -1030,19 +1055,17 @@ __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)
         const LiveBatch& rec2 = recs[v2];
         if (pairable(rec2) && rect_area(rec) + rect_area(rec2) <= TILE_MAX) {
           mask &= mask - 1;
-          render_pair(rec, a.v[v], rec2, a.v[v2], st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift,
-                      natom);
+          render_pair(rec, a.v[v], rec2, a.v[v2], st, tile, tid, wave, lane, publish, grab, &s_next, slice, cut, natom);
           publish = false;
           continue;
         }
       }
       const ViewOut& vo = a.v[v];
-      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, p & in_batch, shift,
-                   nt + nd >= gridDim.x, natom);
+      render_batch(rec, vo.W, vo.H, vo.vb, st, tile, tid, wave, lane, publish, grab, &s_next, slice, cut, natom);
       publish = false;
     }
-    p = uni(s_next);
-    i = live_slot(p >> shift, nt, nd, rate, a.cap);
+    cut.at(uni(s_next), item, slice);
+    i = live_slot(item, nt, nd, rate, a.cap);
   }
   add_atomics<CNT>(a.stats, natom, lane);
 }
