@@ -185,11 +185,11 @@ enum {
  * and atomics of one wave then rarely hit the same tile entries, which
  * shortens the queues on them (the render and two-view passes are faster;
  * pr_resolve's colour gather is a little less coherent).  perm and colors
- * follow the stored order.  Synchronises the
- * stream once (twice where the leading bits of the codes leave too many
- * points together, as in a dense spot or beside a few points far from all
- * others: the sort then goes on over every bit).  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for
- * an unknown order. */
+ * follow the stored order.  Synchronises the stream once (twice where the
+ * leading bits of the codes leave too many points together, as in a dense
+ * spot or beside a few points far from all others: the sort then goes on over
+ * every bit).  PR_ENONFINITE if any coordinate is NaN or Inf, PR_EINVAL for an
+ * unknown order. */
 pr_status pr_build_batches(pr_ctx* ctx, pr_cloud* cloud, uint32_t batch_size, int morton);
 
 /* One view of a multi-view render: matrices and image size as for

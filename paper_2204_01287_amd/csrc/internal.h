@@ -45,8 +45,8 @@ static_assert(sizeof(LiveBatch) == 80, "live batch record is 80 bytes");
 // live batches are handed out through RENDER_QUEUES work queues (queue q
 // owns queue positions q, q + RENDER_QUEUES, ...), each counter on its own
 // 128-byte line: one shared counter serialises every workgroup's request.
-// A position maps to a live-list slot with the untiled batches spread evenly
-// among the tiled ones (live_slot in raster_core.h).
+// A position maps to a live-list slot with the batches that are not tiled
+// (banded and untiled ones) spread evenly among the tiled ones (live_slot in raster_core.h).
 constexpr uint32_t RENDER_QUEUES = 8;
 // A 10-bit batch whose tile rectangle exceeds the tile but is at most one
 // tile wide and max_bands tiles large is rendered in bands of rows that fit
@@ -55,10 +55,10 @@ constexpr uint32_t DEFAULT_BANDS = 4, MAX_BANDS = 64;
 // Slices that a batch of a frame with few batches is cut into at most (raster_core.h).
 constexpr uint32_t MAX_SLICE_SHIFT = 4, MAX_SLICES = 1u << MAX_SLICE_SHIFT;
 struct FrameHeader {
-  // One 64-bit counter (classify adds tiled | untiled << 32 with one atomic
+  // One 64-bit counter (classify adds tiled | others << 32 with one atomic
   // per wave, so the two prefixes it returns come from one order):
   uint32_t live_count;    // tiled live batches / runs with a tiled view, stored from the front of the list
-  uint32_t direct_count;  // untiled live batches / runs with no tiled view, stored from the back
+  uint32_t direct_count;  // banded and untiled live batches / runs with no tiled view, stored from the back
   uint32_t pad[30];
   uint32_t queue[RENDER_QUEUES][32];  // queue[q][0]: next position of queue q
 };

@@ -17,11 +17,11 @@
 // Sec. 3.2 / 3.3 for every batch at once (one thread per batch): it projects
 // the 8 box corners, culls, picks the precision level, folds the decode into
 // the batch matrix, and appends the surviving batches to a compact list with
-// a wave ballot (tiled batches from its front, untiled ones from its back).
+// a wave ballot (tiled batches from its front, the others from its back).
 // The persistent render kernel then hands the live batches to its workgroups
-// through atomic work queues, the untiled ones (whose points go to the global
-// atomic minimum one by one) spread evenly over the frame: concentrated, their
-// atomics contend and the frame is slower.  Classes:
+// through atomic work queues, those that are not tiled spread evenly over the
+// frame: concentrated, the global atomics of the untiled ones (one by one, per
+// point) contend and the frame is slower.  Classes:
 //  CULLED  : some frustum plane has all corners outside by a margin that
 //            exceeds every rounding of the per-point evaluation;
 //  INSIDE  : all corners strictly inside every plane by that margin and w in
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256) k_classify(RenderArgs a) {
       if (words) atomicAdd((unsigned long long*)&a.stats[ST_WORDS], words);
     }
   }
-  // tiled batches from the front of the list, untiled ones from the back, and
+  // tiled batches from the front of the list, the others from the back, and
   // every live batch's slot into the batch-order index (for the shading
   // pass): the wave's prefix there is the sum of its two list prefixes
   const bool tiled = live && ((out.mode >> 16) & 1u);

@@ -952,10 +952,10 @@ __device__ __forceinline__ void render_pair(const LiveBatch& ra, const ViewOut& 
 }
 
 // The live list (or run list) of nb slots holds nt tiled entries from the
-// front and nd entries with untiled batches from the back (slots nb - 1,
-// nb - 2, ...).  Queue position p of n = nt + nd takes an untiled one iff
+// front and nd entries with banded or untiled batches from the back (slots
+// nb - 1, nb - 2, ...).  Item p of n = nt + nd is one of these iff
 // floor((p + 1) m / 2^32) > floor(p m / 2^32), m = ceil(2^32 nd / n), which
-// spreads the untiled batches (and their global atomics) evenly over the frame:
+// spreads them (and their global atomics) evenly over the frame:
 // n m / 2^32 lies in [nd, nd + 1), so exactly nd positions do.  Two high
 // products per position: the exact quotient floor(p nd / n) cost wave 0 a
 // 64-bit division per batch, at one instruction per 8 cycles, while three
